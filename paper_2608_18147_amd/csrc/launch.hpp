@@ -143,6 +143,7 @@ struct SweepSolve {
                    // (launch_sweep_argmins), when it holds (I + 1) x ld int32
     size_t kbytes = 0;  // bytes at K
     int32_t* st;   // traceback state, 264 int32
+    char* B;       // layers_scratch_bytes(p)
     int64_t ld;    // >= p
     int32_t I;     // last layer, min(s, p), 2..255
     double lamp;   // lambda' in MSE units (when lampp is null)
@@ -164,6 +165,11 @@ hipError_t launch_sweep_argmins(const SweepSolve& S, hipStream_t st);
 // MSE / H(I,B) accumulators of every layer into M, Ph (same layout as F);
 // needs the argmins in K.
 hipError_t launch_sweep_accumulators(const SweepSolve& S, double* M, double* Ph, hipStream_t st);
+
+// ---- layers.hip ----
+// F of layers 2..I by the layers with bounds (p >= 2), in S.B's scratch.
+size_t layers_scratch_bytes(int64_t d);
+hipError_t launch_layers(const SweepSolve& S, hipStream_t st);
 
 // ---- search.hip ----
 // The budget search on lambda (Sec. 3 and Sec. 5), kept in device memory and

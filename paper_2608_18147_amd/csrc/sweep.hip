@@ -1223,7 +1223,7 @@ size_t counter_bytes(int64_t p) {
 }
 
 bool sweep_ok(const SweepSolve& S) {
-    return S.I >= 2 && S.I <= 255 && S.H.p >= 2 && S.ld >= S.H.p && S.F && S.Q && S.K && S.st &&
+    return S.I >= 2 && S.I <= 255 && S.H.p >= 2 && S.ld >= S.H.p && S.F && S.Q && S.K && S.B && S.st &&
            S.kbytes >= counter_bytes(S.H.p) && S.kbytes >= trace_scratch_bytes(S.H.p);
 }
 
@@ -1246,13 +1246,24 @@ size_t sweep_scratch_bytes(int64_t d) {
 
 size_t sweep_cost_bytes() { return (size_t)kQAll * sizeof(double); }
 
+// Above these sizes the layers with bounds (launch_layers) take the sweep's
+// place: their launches (one per layer, 5 - 10 us when little is left to
+// evaluate) cost more than the sweep's chain of blocks while there are few
+// values for each layer.  Sweep against layers: 4999 values, 16 layers 0.61 /
+// 0.37 ms, 64 layers 1.2 / 1.4 ms; 12 000 values, 200 layers 6.0 / 6.3 ms;
+// 24 000, 64 layers 5.9 / 3.2 ms; 2^18, 32 layers 134 / 7.9 ms.
+constexpr int64_t kLayersMinP = 4096;
+constexpr int64_t kLayersPerLayer = 64;
+
 hipError_t launch_sweep(const SweepSolve& S, int32_t exact_s, double* out, int32_t* chain,
                         hipStream_t st) {
     if (!sweep_ok(S) || !out) return hipErrorInvalidValue;
     const SweepArgs a = make_args(S);
     const int32_t L = a.I - 2;  // recursive layers 3..I
     hipError_t e;
-    if (L <= 8)
+    if (a.H.p > kLayersMinP && a.H.p > kLayersPerLayer * a.I)
+        e = launch_layers(S, st);
+    else if (L <= 8)
         e = sweep_launch<8>(a, st);
     else if (L <= 16 || ECASQ_SWEEP_LG_MAX == 16)
         e = sweep_launch<16>(a, st);
