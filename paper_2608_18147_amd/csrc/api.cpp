@@ -1346,25 +1346,19 @@ ecasq_status ecasq_encode(const uint8_t* symbols, int64_t d, int32_t t, void* st
         return ECASQ_EINVAL;
     if (capacity < rans_bound(d, t)) return ECASQ_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    const size_t sb = rans_scratch_bytes(d);
     void* mem = nullptr;
-    if (hipMallocAsync(&mem, sb + 512, st) != hipSuccess) return ECASQ_ENOMEM;
-    char* base = static_cast<char*>(mem);
-    auto* bad = reinterpret_cast<unsigned int*>(base + sb);
-    auto* total = reinterpret_cast<unsigned long long*>(base + sb + 256);
-    unsigned long long tot = 0;
-    unsigned int nbad = 0;
+    if (hipMallocAsync(&mem, rans_scratch_bytes(d), st) != hipSuccess) return ECASQ_ENOMEM;
+    const RansResult* res = nullptr;
+    RansResult got{};
     ecasq_status rc = ECASQ_OK;
-    if (hipMemsetAsync(bad, 0, sizeof(unsigned int), st) != hipSuccess ||
-        launch_rans_encode(symbols, d, t, out, base, total, bad, st) != hipSuccess ||
-        hipMemcpyAsync(&tot, total, sizeof tot, hipMemcpyDeviceToHost, st) != hipSuccess ||
-        hipMemcpyAsync(&nbad, bad, sizeof nbad, hipMemcpyDeviceToHost, st) != hipSuccess)
+    if (launch_rans_encode(symbols, d, t, out, static_cast<char*>(mem), &res, st) != hipSuccess ||
+        hipMemcpyAsync(&got, res, sizeof got, hipMemcpyDeviceToHost, st) != hipSuccess)
         rc = ECASQ_EHIP;
     if (hipFreeAsync(mem, st) != hipSuccess) rc = ECASQ_EHIP;
     if (hipStreamSynchronize(st) != hipSuccess) rc = ECASQ_EHIP;
     if (rc != ECASQ_OK) return rc;
-    if (nbad) return ECASQ_EINVAL;
-    *out_bytes = 2 * (int64_t)t + 4 * rans_segments(d) + (int64_t)tot;
+    if (got.bad) return ECASQ_EINVAL;
+    *out_bytes = 2 * (int64_t)t + 4 * rans_segments(d) + (int64_t)got.total;
     return ECASQ_OK;
 }
 

@@ -86,3 +86,44 @@ def test_rans_rejects_malformed_input():
         ecasq.ecasq_decode(data[: data.numel() - 3], len(sym), 5)   # truncated
     back = ecasq.ecasq_decode(data, len(sym), 5)
     np.testing.assert_array_equal(back.cpu().numpy(), sym.astype(np.uint8))
+
+
+@pytest.mark.parametrize("d", [1, 15, 16, 17, 4095, 4097, 4 * rans.SEG + 31, 1025 * rans.SEG + 3])
+@pytest.mark.parametrize("t", [2, 5, 256])
+def test_rans_edges(d, t):
+    """One symbol to more segments than wavefronts (two to a wavefront), parts
+    of the 16-symbol groups, symbols that share an entry of the decoding table
+    (t = 256: most have a frequency of 1 to 3), and starts that are not aligned."""
+    _say("rans edges", d, t)
+    rng = np.random.default_rng(63 + d + t)
+    p = np.full(t, 1e-5)
+    p[t // 2] = 1.0
+    sym = rng.choice(t, size=d + 3, p=p / p.sum()).astype(np.uint8)
+    if d < 100:
+        sym = rng.integers(0, t, size=d + 3).astype(np.uint8)
+    dev = _dev_u8(sym)[3:]
+    g = ecasq.ecasq_encode(dev, t)
+    if d < 100000:
+        assert bytes(g.cpu().numpy().tobytes()) == rans.encode(list(sym[3:]), t)
+    shifted = torch.empty(g.numel() + 1, dtype=torch.uint8, device="cuda")[1:]
+    shifted.copy_(g)
+    assert torch.equal(ecasq.ecasq_decode(shifted, d, t), dev)
+
+
+def test_rans_start_below_l():
+    """A stream whose first state is below L (no encoder writes one): the first
+    symbol then takes as many bytes as it needs.  State 1 decodes to symbol 0
+    and leaves 1, which three bytes bring to the start of an ordinary stream
+    whose state begins with the byte 1."""
+    _dev_u8([0])
+    for seed in range(4000):
+        sym = np.random.default_rng(seed).integers(0, 3, size=40)
+        o = rans.encode(list(sym), 3)
+        if o[10] == 1:
+            break
+    assert o[10] == 1  # after 3 frequencies and the segment's end
+    end = int.from_bytes(o[6:10], "little")
+    raw = o[:6] + (end + 3).to_bytes(4, "little") + bytes([0, 0, 0]) + o[10:]
+    data = torch.tensor(list(raw), dtype=torch.uint8, device="cuda")
+    back = ecasq.ecasq_decode(data, 41, 3)
+    np.testing.assert_array_equal(back.cpu().numpy(), np.concatenate([[0], sym]))
