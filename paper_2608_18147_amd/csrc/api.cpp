@@ -1389,6 +1389,11 @@ ecasq_status ecasq_quantize(const void* x, ecasq_dtype dt, int64_t d, const doub
     ECASQ_TRY(check_x(x, dt, d));
     if (!codebook || t < 1 || t > 256 || !symbols || !empirical_entropy) return ECASQ_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (quantize_is_small(d)) {
+        HIP_TRY(launch_quantize_small(x, dt, d, codebook, t, seed, symbols, empirical_entropy,
+                                      hist, st));
+        return ECASQ_OK;
+    }
     void* h = nullptr;
     if (hipMallocAsync(&h, sizeof(unsigned long long) * 256, st) != hipSuccess)
         return ECASQ_ENOMEM;
@@ -1409,6 +1414,11 @@ ecasq_status ecasq_quantize_noalloc(const void* x, ecasq_dtype dt, int64_t d,
     ECASQ_TRY(check_x(x, dt, d));
     if (!codebook || t < 1 || t > 256 || !symbols || !empirical_entropy) return ECASQ_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
+    if (quantize_is_small(d)) {
+        HIP_TRY(launch_quantize_small(x, dt, d, codebook, t, seed, symbols, empirical_entropy,
+                                      hist, st));
+        return ECASQ_OK;
+    }
     unsigned long long* hh = nullptr;
     HIP_TRY(quantize_scratch(&hh));
     HIP_TRY(launch_zero_counts(hh, t, st));
