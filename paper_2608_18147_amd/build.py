@@ -14,7 +14,7 @@ import sys
 HERE = os.path.dirname(os.path.abspath(__file__))
 CSRC = os.path.join(HERE, "csrc")
 LIB = os.path.join(HERE, "libecasq.so")
-SOURCES = ["prep.hip", "alphabet.hip", "dp.hip", "sweep.hip", "layers.hip", "opt.hip", "post.hip",
+SOURCES = ["prep.hip", "alphabet.hip", "dp.hip", "sweep.hip", "layers.hip", "held.hip", "opt.hip", "post.hip",
            "rans.hip", "batched.hip", "search.hip", "api.cpp"]
 ARCH = os.environ.get("ECASQ_OFFLOAD_ARCH", "gfx950")
 HIPCC = os.environ.get("HIPCC", "/opt/rocm/bin/hipcc")
@@ -31,6 +31,7 @@ FLAGS = [
 # quiets every loop-carried operand of fmin (one extra fp64 max per layer and
 # predecessor, about a fifth of the kernel's instructions).
 EXTRA_FLAGS = {"sweep.hip": ["-fno-honor-nans"], "layers.hip": ["-fno-honor-nans"],
+               "held.hip": ["-fno-honor-nans"],
                "batched.hip": ["-fno-honor-nans"]}
 
 

@@ -23,7 +23,10 @@
 // of each).
 //
 // What bounds it: the way of a value from one workgroup to another and the
-// reduction, about HELD_US us a layer.
+// reduction, 1.6 us a layer at 1024 values, 2.6 at 3071 and 4.4 at 4096 (more
+// workgroups than places: two rounds).  A solve of 4096 values and 64 layers takes
+// 275 us where the column-block sweep takes 810, one of 1024 and 16 layers 25
+// where it takes 86.
 #include "device.hpp"
 #include "launch.hpp"
 

@@ -174,6 +174,11 @@ hipError_t launch_sweep_accumulators(const SweepSolve& S, double* M, double* Ph,
 size_t layers_scratch_bytes(int64_t d);
 hipError_t launch_layers(const SweepSolve& S, hipStream_t st);
 
+// ---- held.hip ----
+// F of layers 2..I with every pair's cost held in registers (2 <= p <= kHeldMaxP).
+constexpr int64_t kHeldMaxP = 4096;
+hipError_t launch_held(const SweepSolve& S, hipStream_t st);
+
 // ---- search.hip ----
 // The budget search on lambda (Sec. 3 and Sec. 5), kept in device memory and
 // advanced by one-thread kernels: after each batch of DP solves the commit

@@ -886,6 +886,35 @@ __global__ __launch_bounds__(kSB* kTileWaves) ECASQ_STEP_ATTR void k_sweep_step(
 // Traceback state (device): st[0] = i*, the chain u_0..u_{i*-1} at st + 8.
 constexpr int kStChain = 8;
 
+// eq. apx_final: the lowest i among the least F_i[p-1] (or I for exactly s
+// values) and that F, in every lane of a wavefront: each lane the lowest of its
+// layers 2 + lane, 66 + lane, ..., then (value, i) minima across lanes.
+__device__ __forceinline__ int32_t pick_layer(const SweepArgs& a, int32_t exact_s, double& bj) {
+    const int64_t p = a.H.p;
+    if (exact_s) {
+        bj = a.F[(int64_t)a.I * a.ld + p - 1];
+        return a.I;
+    }
+    bj = __builtin_huge_val();
+    int32_t bi = 0x7fffffff;
+    for (int32_t i = 2 + (int32_t)(threadIdx.x % kSB); i <= a.I; i += kSB) {
+        const double f = a.F[(int64_t)i * a.ld + p - 1];
+        if (bi == 0x7fffffff || f < bj) {
+            bj = f;
+            bi = i;
+        }
+    }
+    for (int off = 32; off >= 1; off >>= 1) {
+        const double ov = __shfl_xor(bj, off);
+        const int32_t oi = __shfl_xor(bi, off);
+        if (ov < bj || (ov == bj && oi < bi)) {
+            bj = ov;
+            bi = oi;
+        }
+    }
+    return __builtin_amdgcn_readfirstlane(bi);
+}
+
 // eq. apx_final on the finished table: i* (the lowest argmin over layers, or
 // I for exactly s values), u_{i*-1} = p - 1, u_0 = 0, out[0] = J.
 // A solve whose steps gave up a wait (failure word set) reports i* = 0: the
@@ -903,30 +932,8 @@ __global__ __launch_bounds__(64) void k_sweep_pick(SweepArgs a, int32_t exact_s,
         }
         return;
     }
-    // the lowest i among the least F_i[p-1]: each lane the lowest of its
-    // layers 2 + lane, 66 + lane, ..., then (value, i) minima across lanes
-    double bj = __builtin_huge_val();
-    int32_t bi = 0x7fffffff;
-    if (exact_s) {
-        bi = a.I;
-        bj = a.F[(int64_t)a.I * a.ld + p - 1];
-    } else {
-        for (int32_t i = 2 + lane; i <= a.I; i += 64) {
-            const double f = a.F[(int64_t)i * a.ld + p - 1];
-            if (bi == 0x7fffffff || f < bj) {
-                bj = f;
-                bi = i;
-            }
-        }
-        for (int off = 32; off >= 1; off >>= 1) {
-            const double ov = __shfl_xor(bj, off);
-            const int32_t oi = __shfl_xor(bi, off);
-            if (ov < bj || (ov == bj && oi < bi)) {
-                bj = ov;
-                bi = oi;
-            }
-        }
-    }
+    double bj;
+    const int32_t bi = pick_layer(a, exact_s, bj);
     if (lane == 0) {
         st[0] = bi;
         st[kStChain + bi - 1] = (int32_t)(p - 1);
@@ -1020,73 +1027,15 @@ __global__ __launch_bounds__(kTrT) void k_sweep_trace_pick(int32_t i, int32_t* _
     if (threadIdx.x == 0) st[kStChain + i - 2] = rk[0];
 }
 
-// The whole traceback in one workgroup, for small p: layer by layer from i*
-// down to 3, the lowest argmin of the chain column's candidates (the same
-// (value, k) pairs as the two kernels above, reduced lexicographically: a
-// butterfly per wavefront, then across the wavefronts in LDS), the next
-// column kept in LDS.  One launch instead of two per layer.
-constexpr int kTrOneT = 1024;
-constexpr int64_t kTrOneMaxP = 16384;  // at most 16 candidates per thread
-
-__global__ __launch_bounds__(kTrOneT) void k_sweep_trace_one(SweepArgs a, int32_t* __restrict__ st) {
-    __shared__ double2 tab[kLog2Size];
-    __shared__ double rv[kTrOneT / kSB];
-    __shared__ int32_t rk[kTrOneT / kSB];
-    __shared__ int32_t jn;
-    if (!sweep_live(a)) return;  // uniform
-    const int32_t n = st[0];
-    if (n < 3) return;  // uniform: no interior value, or a failed solve (0)
-    load_log2_table(tab);
-    if (threadIdx.x == 0) jn = st[kStChain + n - 1];
-    __syncthreads();
-    const int lane = threadIdx.x % kSB, wave = threadIdx.x / kSB;
-    for (int32_t i = n; i >= 3; i--) {
-        const int64_t j = jn;
-        const double* Fp = a.F + (int64_t)(i - 1) * a.ld;
-        double best = __builtin_huge_val();
-        int32_t bk = INT32_MAX;
-        for (int64_t k = (i - 2) + (int64_t)threadIdx.x; k < j; k += kTrOneT) {
-            double C, P;
-            cell_at(a.H, k, j, tab, C, P);
-            lexmin(best, bk, Fp[k] + __builtin_fma(-a.lamp, P, C), (int32_t)k);
-        }
-#pragma unroll
-        for (int off = kSB / 2; off > 0; off >>= 1)
-            lexmin(best, bk, __shfl_xor(best, off), __shfl_xor(bk, off));
-        if (lane == 0) {
-            rv[wave] = best;
-            rk[wave] = bk;
-        }
-        __syncthreads();
-        if (wave == 0) {
-            best = lane < kTrOneT / kSB ? rv[lane] : __builtin_huge_val();
-            bk = lane < kTrOneT / kSB ? rk[lane] : INT32_MAX;
-#pragma unroll
-            for (int off = kSB / 2; off > 0; off >>= 1)
-                lexmin(best, bk, __shfl_xor(best, off), __shfl_xor(bk, off));
-            if (lane == 0) {
-                st[kStChain + i - 2] = bk;
-                jn = bk;
-            }
-        }
-        __syncthreads();
-    }
-}
-
-// The chain's MSE and H(I,B) summed in path order.  One wavefront.
-// out: J (already written), MSE, H(I,B), i*.
-__global__ __launch_bounds__(kSB) void k_sweep_sums(SweepArgs a, const int32_t* __restrict__ st,
-                                                    double* out, int32_t* chain_out) {
-    __shared__ double2 tab[kLog2Size];
-    __shared__ double cC[256], cP[256];
-    if (!sweep_live(a)) return;
-    load_log2_table(tab);
-    __syncthreads();
-    const int lane = threadIdx.x;
-    const int32_t n = st[0];
-    const int32_t* u = st + kStChain;
+// MSE and H(I,B) of the chain u_0 .. u_{n-1}, summed in path order, by one
+// wavefront (cC, cP: LDS).  out: J (already written), MSE, H(I,B), i*.
+__device__ __forceinline__ void path_sums(const SweepArgs& a, const double2* __restrict__ tab,
+                                          const int32_t* u, int32_t n, double* cC, double* cP,
+                                          double* out, int32_t* chain_out) {
+    const int lane = threadIdx.x % kSB;
     for (int r = lane; r + 1 < n; r += kSB) cell_at(a.H, u[r], u[r + 1], tab, cC[r], cP[r]);
-    __syncthreads();
+    __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
+    __builtin_amdgcn_wave_barrier();
     if (lane == 0) {
         double mse = 0.0, ph = 0.0;
         for (int r = 0; r + 1 < n; r++) {
@@ -1099,6 +1048,157 @@ __global__ __launch_bounds__(kSB) void k_sweep_sums(SweepArgs a, const int32_t* 
     }
     if (chain_out)
         for (int r = lane; r < n; r += kSB) chain_out[r] = u[r];
+}
+
+__global__ __launch_bounds__(kSB) void k_sweep_sums(SweepArgs a, const int32_t* __restrict__ st,
+                                                    double* out, int32_t* chain_out) {
+    __shared__ double2 tab[kLog2Size];
+    __shared__ double cC[256], cP[256];
+    if (!sweep_live(a)) return;
+    load_log2_table(tab);
+    __syncthreads();
+    path_sums(a, tab, st + kStChain, st[0], cC, cP, out, chain_out);
+}
+
+// The choice of i*, the whole traceback and the path's sums in one workgroup, for
+// p <= kTrOneMaxP (one launch; with more values the candidates of a column
+// are worth several workgroups).  Layer by layer from i* down to 3, the lowest
+// argmin of the chain column's candidates (the same (value, k) pairs as the
+// two kernels above, reduced lexicographically: a butterfly per wavefront,
+// then across the wavefronts).  F_i[j] is known, the least candidate: one
+// whose F_{i-1}[k] + C alone lies above it is not evaluated (the operations
+// are monotone, and -P >= -2^-20: U + D <= d, and the rounding of U / d and D / d is
+// below 2^-53 |v_j| / (v_j - v_k) <= 2^-28 for 24-bit values), which leaves a
+// few.  The thread's predecessors (p <= kTrT1 kTrR1) stay in registers, those of F_{i-2} are
+// loaded while layer i is reduced, and the chosen predecessor's own thread
+// hands out its values for the next layer.
+constexpr int kTrT1 = 1024;
+constexpr int kTrR1 = 4;
+constexpr int64_t kTrOneMaxP = 16384;
+
+template <bool HELD>
+__global__ __launch_bounds__(kTrT1) void k_sweep_finish(SweepArgs a, int32_t exact_s, double* out,
+                                                        int32_t* chain_out) {
+    constexpr int W = kTrT1 / kSB;
+    __shared__ double2 tab[kLog2Size];
+    __shared__ double rv[2][W], col[2][5], cC[256], cP[256];
+    __shared__ int32_t rk[2][W], u[256];
+    if (!sweep_live(a)) return;  // uniform
+    const int tid = threadIdx.x, lane = tid % kSB, wave = tid / kSB;
+    const int64_t p = a.H.p;
+    load_log2_table(tab);
+    if (a.K[a.nblk] != 0) {  // uniform: a failed solve
+        if (tid == 0) {
+            out[0] = __builtin_huge_val();
+            out[1] = out[2] = out[3] = 0.0;
+        }
+        return;
+    }
+    double bj;
+    const int32_t n = pick_layer(a, exact_s, bj);  // in every wavefront
+    double v[kTrR1], N[kTrR1], S[kTrR1], S2[kTrR1], f[kTrR1];
+    auto row = [&](int32_t i) {  // F_i of the thread's predecessors
+        if (i < 2) return;
+#pragma unroll
+        for (int r = 0; r < kTrR1; r++) {
+            const int64_t k = tid + kTrT1 * r;
+            f[r] = k < p ? a.F[(int64_t)i * a.ld + k] : __builtin_huge_val();
+        }
+    };
+    if constexpr (HELD) {
+#pragma unroll
+        for (int r = 0; r < kTrR1; r++) {
+            const int64_t k = min((int64_t)tid + kTrT1 * r, p - 1);
+            v[r] = a.H.v[k];
+            N[r] = a.H.N[k];
+            S[r] = a.H.S[k];
+            S2[r] = a.H.S2[k];
+        }
+        row(n - 1);
+    }
+    if (tid == 0) {
+        out[0] = bj;
+        u[n - 1] = (int32_t)(p - 1);
+        u[0] = 0;
+        col[n & 1][0] = a.H.v[p - 1];
+        col[n & 1][1] = a.H.N[p - 1];
+        col[n & 1][2] = a.H.S[p - 1];
+        col[n & 1][3] = a.H.S2[p - 1];
+        col[n & 1][4] = bj;
+    }
+    __syncthreads();
+    int32_t j = (int32_t)(p - 1);
+    const double slack = a.lamp * 0x1p-17;
+    for (int32_t i = n; i >= 3; i--) {
+        const double* c = col[i & 1];
+        const double jv = c[0], jN = c[1], jS = c[2], jS2 = c[3], least = c[4];
+        double best = __builtin_huge_val();
+        int32_t bk = INT32_MAX;
+        auto look = [&](int64_t k, double kv, double kN, double kS, double kS2, double kf) {
+            if (k < i - 2 || k >= j) return;
+            const double C0 = cell_c(kv, kN, kS, kS2, jv, jN, jS, jS2);
+            if (kf + (C0 - slack) > least) {
+                const double kn = jN - kN, sa = jS - kS, lim = (jv - kv) * a.H.dd * (1.0 + 0x1p-20);
+                if (__builtin_fma(-kv, kn, sa) <= lim && __builtin_fma(jv, kn, -sa) <= lim) return;
+            }
+            double C, P;
+            cell_terms(kv, kN, kS, kS2, jv, jN, jS, jS2, a.H.dd, false, 0.0, tab, C, P);
+            lexmin(best, bk, kf + __builtin_fma(-a.lamp, P, C), (int32_t)k);
+        };
+        double fo[kTrR1];
+        if constexpr (HELD) {
+#pragma unroll
+            for (int r = 0; r < kTrR1; r++) {
+                look(tid + kTrT1 * r, v[r], N[r], S[r], S2[r], f[r]);
+                fo[r] = f[r];
+            }
+            row(i - 2);
+        } else {
+            const double* Fp = a.F + (int64_t)(i - 1) * a.ld;
+#pragma unroll 4
+            for (int64_t k = tid; k < j; k += kTrT1)
+                look(k, a.H.v[k], a.H.N[k], a.H.S[k], a.H.S2[k], Fp[k]);
+        }
+#pragma unroll
+        for (int off = kSB / 2; off > 0; off >>= 1)
+            lexmin(best, bk, __shfl_xor(best, off), __shfl_xor(bk, off));
+        if (lane == 0) {
+            rv[i & 1][wave] = best;
+            rk[i & 1][wave] = bk;
+        }
+        __syncthreads();
+        best = rv[i & 1][lane % W];
+        bk = rk[i & 1][lane % W];
+#pragma unroll
+        for (int off = W / 2; off > 0; off >>= 1)
+            lexmin(best, bk, __shfl_xor(best, off), __shfl_xor(bk, off));
+        j = __builtin_amdgcn_readfirstlane(bk);
+        double* o = col[(i - 1) & 1];
+        if (tid == 0) u[i - 2] = j;
+        if (j < 0 || j >= p) {  // uniform; a column without a finite candidate (not reached)
+            if (tid == 0) out[1] = out[2] = out[3] = 0.0;
+            return;
+        }
+        if constexpr (HELD) {
+#pragma unroll
+            for (int r = 0; r < kTrR1; r++)
+                if (tid + kTrT1 * r == j) {
+                    o[0] = v[r];
+                    o[1] = N[r];
+                    o[2] = S[r];
+                    o[3] = S2[r];
+                    o[4] = fo[r];
+                }
+        } else if (tid == 0) {
+            o[0] = a.H.v[j];
+            o[1] = a.H.N[j];
+            o[2] = a.H.S[j];
+            o[3] = a.H.S2[j];
+            o[4] = a.F[(int64_t)(i - 1) * a.ld + j];
+        }
+        __syncthreads();
+    }
+    if (wave == 0) path_sums(a, tab, u, n, cC, cP, out, chain_out);
 }
 
 // Argmins of layer i at every valid column (inspection only): one column per
@@ -1252,8 +1352,14 @@ size_t sweep_cost_bytes() { return (size_t)kQAll * sizeof(double); }
 // values for each layer.  Sweep against layers: 4999 values, 16 layers 0.61 /
 // 0.37 ms, 64 layers 1.2 / 1.4 ms; 12 000 values, 200 layers 6.0 / 6.3 ms;
 // 24 000, 64 layers 5.9 / 3.2 ms; 2^18, 32 layers 134 / 7.9 ms.
-constexpr int64_t kLayersMinP = 4096;
+constexpr int64_t kLayersMinP = kHeldMaxP;
 constexpr int64_t kLayersPerLayer = 64;
+
+// Up to kHeldMaxP values the costs fit in registers (launch_held).  Below
+// kHeldMinP values, or few for each layer, the sweep's chain of blocks is shorter than
+// a hand-over between workgroups for every layer.
+constexpr int64_t kHeldMinP = 256;
+constexpr int64_t kHeldPerLayer = 4;
 
 hipError_t launch_sweep(const SweepSolve& S, int32_t exact_s, double* out, int32_t* chain,
                         hipStream_t st) {
@@ -1263,6 +1369,8 @@ hipError_t launch_sweep(const SweepSolve& S, int32_t exact_s, double* out, int32
     hipError_t e;
     if (a.H.p > kLayersMinP && a.H.p > kLayersPerLayer * a.I)
         e = launch_layers(S, st);
+    else if (a.H.p <= kHeldMaxP && a.H.p > kHeldMinP && a.H.p > kHeldPerLayer * a.I)
+        e = launch_held(S, st);
     else if (L <= 8)
         e = sweep_launch<8>(a, st);
     else if (L <= 16 || ECASQ_SWEEP_LG_MAX == 16)
@@ -1272,11 +1380,13 @@ hipError_t launch_sweep(const SweepSolve& S, int32_t exact_s, double* out, int32
     else
         e = sweep_launch<32>(a, st);
     if (e != hipSuccess) return e;
-    k_sweep_pick<<<1, 64, 0, st>>>(a, exact_s, out, S.st);
-    // traceback: layers above i* return at once; small p in one launch
-    if (a.H.p <= kTrOneMaxP) {
-        k_sweep_trace_one<<<1, kTrOneT, 0, st>>>(a, S.st);
+    if (a.H.p <= kTrT1 * kTrR1) {
+        k_sweep_finish<true><<<1, kTrT1, 0, st>>>(a, exact_s, out, chain);
+    } else if (a.H.p <= kTrOneMaxP) {
+        k_sweep_finish<false><<<1, kTrT1, 0, st>>>(a, exact_s, out, chain);
     } else {
+        k_sweep_pick<<<1, 64, 0, st>>>(a, exact_s, out, S.st);
+        // traceback: layers above i* return at once
         const int32_t g = trace_groups(a.H.p);
         double* pv = reinterpret_cast<double*>(S.K);
         int32_t* pk = reinterpret_cast<int32_t*>(pv + g);
@@ -1284,8 +1394,8 @@ hipError_t launch_sweep(const SweepSolve& S, int32_t exact_s, double* out, int32
             k_sweep_trace_part<<<(unsigned)g, kTrT, 0, st>>>(a, i, S.st, pv, pk);
             k_sweep_trace_pick<<<1, kTrT, 0, st>>>(i, S.st, pv, pk, g, S.runp);
         }
+        k_sweep_sums<<<1, kSB, 0, st>>>(a, S.st, out, chain);
     }
-    k_sweep_sums<<<1, kSB, 0, st>>>(a, S.st, out, chain);
     return hipGetLastError();
 }
 
