@@ -17,18 +17,32 @@ constexpr int kMaxT = 256;
 
 // The whole refinement in one block: rounds of colour substeps 0, 1, 2.  All
 // movers of a colour are independent (their objectives share no frequency)
-// and are searched in parallel, one thread each; a substep whose result
+// and are searched in parallel; a substep whose result
 // violates the budget (budget mode) is undone; refinement stops after a round
 // without a committed move.  stats: rounds run, moves committed.
-__global__ __launch_bounds__(256) void k_refine(Hist H, int32_t t, int32_t* __restrict__ ug,
-                                                double lamp, double b, int32_t budget,
-                                                int32_t rounds, int32_t exhaustive,
-                                                int32_t* __restrict__ stats) {
+//
+// One evaluation of the objective is a chain of loads, divisions and logarithms of
+// about half a microsecond, and a mover's binary search takes two of them for each of its log2(p) steps.
+// 16 lanes search for a mover together: they evaluate both sides of all 7
+// comparisons that the next three steps may ask for, so that three steps cost one evaluation.  The
+// comparisons and their outcomes are those of the one-by-one search.  The
+// entropy of the budget check is formed one value per thread and summed in order by
+// one.
+constexpr int kRefT = 1024;
+constexpr int kRefG = 16;  // lanes of a mover
+
+__global__ __launch_bounds__(kRefT) void k_refine(Hist H, int32_t t, int32_t* __restrict__ ug,
+                                                  double lamp, double b, int32_t budget,
+                                                  int32_t rounds, int32_t exhaustive,
+                                                  int32_t* __restrict__ stats) {
     __shared__ double2 tab[kLog2Size];
     __shared__ int32_t u[kMaxT], nu[kMaxT];
     __shared__ int32_t moved_s, commit_s;
-    __shared__ double redv[256];
-    __shared__ int64_t redi[256];
+    __shared__ double redv[kRefT];
+    __shared__ int64_t redi[kRefT];
+    double* sU = redv;  // (the reduction arrays are free when these are used)
+    double* sD = redv + kMaxT;
+    double* sh = redv + 2 * kMaxT;
     const int tid = threadIdx.x;
     load_log2_table(tab);
     for (int r = tid; r < t; r += blockDim.x) u[r] = ug[r];
@@ -41,23 +55,48 @@ __global__ __launch_bounds__(256) void k_refine(Hist H, int32_t t, int32_t* __re
             if (tid == 0) moved_s = 0;
             __syncthreads();
             if (!exhaustive) {
-                for (int32_t r = 1 + tid; r <= t - 2; r += blockDim.x) {
-                    if (r % 3 != c) continue;
+                const int sub = tid % kRefG;
+                // the first mover of the colour is c, or 3 for colour 0
+                for (int32_t r = (c ? c : 3) + 3 * (tid / kRefG); r <= t - 2;
+                     r += 3 * (kRefT / kRefG)) {
                     const int64_t L = u[r - 1], R = u[r + 1];
                     if (R - L < 3) continue;
                     int64_t lo = L + 1, hi = R - 1;
                     while (lo < hi) {
-                        const int64_t mid = lo + (hi - lo) / 2;
-                        if (refine_local(H, t, u, r, mid + 1, lamp, tab) <
-                            refine_local(H, t, u, r, mid, lamp, tab))
-                            lo = mid + 1;
-                        else
-                            hi = mid;
+                        // lane 2 x + s evaluates side s of comparison x of the tree: x = 0
+                        // the next one, 2 x + 1 and 2 x + 2 those that follow its outcomes
+                        int64_t a = lo, e = hi;
+                        const int x1 = sub / 2 + 1;  // 1 b1 b2: the outcomes on the way
+                        for (int bit = 30 - __builtin_clz((unsigned)x1); bit >= 0; bit--) {
+                            const int64_t mid = a + (e - a) / 2;
+                            if (a >= e) break;
+                            if ((x1 >> bit) & 1) a = mid + 1;
+                            else e = mid;
+                        }
+                        const bool on = a < e && sub < 14;
+                        const int64_t m = on ? a + (e - a) / 2 + (sub & 1) : lo;
+                        const double val = refine_local(H, t, u, r, m, lamp, tab);
+                        const double other = __shfl_xor(val, 1);
+                        const uint32_t less =
+                            (uint32_t)(__ballot((sub & 1) == 0 && other < val) >>
+                                       (tid % 64 / kRefG * kRefG)) & 0xFFFFu;
+                        int x = 0;
+                        for (int step = 0; step < 3 && lo < hi; step++) {
+                            const int64_t mid = lo + (hi - lo) / 2;
+                            const bool up = (less >> (2 * x)) & 1u;
+                            if (up) lo = mid + 1;
+                            else hi = mid;
+                            x = 2 * x + (up ? 2 : 1);
+                        }
                     }
-                    if (lo != u[r] && refine_local(H, t, u, r, lo, lamp, tab) <
-                                          refine_local(H, t, u, r, u[r], lamp, tab)) {
-                        nu[r] = (int32_t)lo;
-                        atomicAdd(&moved_s, 1);
+                    if (lo != u[r]) {
+                        const double val =
+                            refine_local(H, t, u, r, sub & 1 ? (int64_t)u[r] : lo, lamp, tab);
+                        const double was = __shfl_xor(val, 1);
+                        if (sub == 0 && val < was) {
+                            nu[r] = (int32_t)lo;
+                            atomicAdd(&moved_s, 1);
+                        }
                     }
                 }
             } else {
@@ -101,9 +140,23 @@ __global__ __launch_bounds__(256) void k_refine(Hist H, int32_t t, int32_t* __re
                 }
             }
             __syncthreads();
+            if (budget && moved_s) {  // uniform
+                // expected frequencies and their terms as chain_hout forms them
+                for (int32_t r = tid; r + 1 < t; r += blockDim.x)
+                    ud_at(H, nu[r], nu[r + 1], sU[r], sD[r]);
+                __syncthreads();
+                for (int32_t r = tid; r < t; r += blockDim.x)
+                    sh[r] = hf(H, r == 0 ? H.c0 + sD[0] : r == t - 1 ? sU[r - 1] : sU[r - 1] + sD[r],
+                               tab);
+                __syncthreads();
+            }
             if (tid == 0) {
                 int32_t moved = moved_s;
-                if (moved && budget && chain_hout(H, t, nu, tab) > b) moved = 0;
+                if (moved && budget) {
+                    double ho = 0.0;
+                    for (int32_t r = 0; r < t; r++) ho = ho + sh[r];
+                    if (ho > b) moved = 0;
+                }
                 commit_s = moved;
             }
             __syncthreads();
@@ -589,7 +642,7 @@ hipError_t launch_zero_counts(unsigned long long* h, int32_t n, hipStream_t st) 
 hipError_t launch_refine(const Hist& H, int32_t t, int32_t* u, double lamp, double b,
                          int32_t budget, int32_t rounds, int32_t exhaustive, int32_t* stats,
                          hipStream_t st) {
-    k_refine<<<1, 256, 0, st>>>(H, t, u, lamp, b, budget, rounds, exhaustive, stats);
+    k_refine<<<1, kRefT, 0, st>>>(H, t, u, lamp, b, budget, rounds, exhaustive, stats);
     return hipGetLastError();
 }
 
