@@ -648,9 +648,7 @@ ecasq_status search_device_loop(Ctx& c, int32_t exact_s, int32_t max_passes) {
     int32_t n = 0;
     for (;;) {
         ECASQ_TRY(sweep_enqueue(c, &S->todo_lamp[0], &S->run, exact_s));
-        HIP_TRY(launch_search_commit(S, res, ch, 1, pch, 1, c.st));
-        HIP_TRY(hipMemcpyAsync(c.poll + (n & 1), &S->peek, sizeof(SearchPeek),
-                               hipMemcpyDeviceToHost, c.st));
+        HIP_TRY(launch_search_commit(S, res, ch, 1, pch, 1, c.poll + (n & 1), c.st));
         HIP_TRY(hipEventRecord(c.ev[n & 1], c.st));
         n++;
         if (n > ahead) {
@@ -689,7 +687,7 @@ ecasq_status search_host_pass(Ctx& c, const SearchState& h, int32_t exact_s) {
             HIP_TRY(hipMemcpyAsync(cres, r, sizeof r, hipMemcpyHostToDevice, c.st));
             HIP_TRY(hipMemcpyAsync(cch, P.chain.data(), sizeof(int32_t) * P.t,
                                    hipMemcpyHostToDevice, c.st));
-            HIP_TRY(launch_search_commit(S, cres, cch, 1, pch, 0, c.st));
+            HIP_TRY(launch_search_commit(S, cres, cch, 1, pch, 0, nullptr, c.st));
         }
         return ECASQ_OK;
     }
@@ -698,7 +696,7 @@ ecasq_status search_host_pass(Ctx& c, const SearchState& h, int32_t exact_s) {
             Point P;
             ECASQ_TRY(sweep_solve(c, h.todo[g], exact_s, P, nullptr, nullptr, 0));
             HIP_TRY(launch_search_commit(S, c.at<double>(c.L.res), c.at<int32_t>(c.L.swchain), 1,
-                                         pch, 0, c.st));
+                                         pch, 0, nullptr, c.st));
         }
         return ECASQ_OK;
     }
@@ -717,7 +715,8 @@ ecasq_status search_host_pass(Ctx& c, const SearchState& h, int32_t exact_s) {
         c.cells = cells0 + (c.cells - cells0) / kMaxLambdas * m;
         c.solves = solves0 + m;
     }
-    HIP_TRY(launch_search_commit(S, c.at<double>(c.L.res), nullptr, m, pch, 0, c.st));
+    HIP_TRY(launch_search_commit(S, c.at<double>(c.L.res), nullptr, m, pch, 0, nullptr,
+                                 c.st));
     return ECASQ_OK;
 }
 

@@ -219,9 +219,11 @@ hipError_t launch_search_begin(SearchState* S, const SearchParams& P, const doub
 // (device) holds 4 doubles per point (J, MSE, H, t); chains (device, stride
 // S->s, may be null) their codebooks, copied into pchains (kSearchMaxPts x s)
 // when S->has_chain.  With gate != 0 the kernel does nothing unless S->run is
-// set (a solve that was skipped because the search had ended).
+// set (a solve that was skipped because the search had ended).  peek_out (pinned
+// host memory, may be null) receives S->peek.
 hipError_t launch_search_commit(SearchState* S, const double* res, const int32_t* chains,
-                                int32_t m, int32_t* pchains, int32_t gate, hipStream_t st);
+                                int32_t m, int32_t* pchains, int32_t gate, SearchPeek* peek_out,
+                                hipStream_t st);
 
 // ---- post.hip ----
 hipError_t launch_refine(const Hist& H, int32_t t, int32_t* u, double lamp, double b,

@@ -20,6 +20,8 @@
 // machine advances through such queries until it needs a real solve: it then
 // lists the multipliers to solve in todo (lambda' = RN(lambda ||X||^2) in
 // todo_lamp) and sets run, or it sets done.
+#include <stddef.h>
+
 #include "device.hpp"
 #include "launch.hpp"
 
@@ -239,16 +241,34 @@ __global__ __launch_bounds__(64) void k_search_begin(SearchState* __restrict__ S
     peek(S);
 }
 
-__global__ __launch_bounds__(64) void k_search_commit(SearchState* __restrict__ Sp,
-                                                      const double* __restrict__ res,
-                                                      const int32_t* __restrict__ chains,
-                                                      int32_t m, int32_t* __restrict__ pchains,
-                                                      int32_t gate) {
+// The state is advanced in LDS: one thread's walk through it, and through the
+// points for each query, is a chain of reads (10 us from memory).  peek_out: pinned
+// host memory for the host's poll (null: not wanted).
+constexpr int kHeadWords = (int)(offsetof(SearchState, pts) / sizeof(uint32_t));
+constexpr int kPtWords = (int)(sizeof(SearchPt) / sizeof(uint32_t));
+static_assert(offsetof(SearchState, pts) % sizeof(uint32_t) == 0 &&
+                  sizeof(SearchPt) % sizeof(uint32_t) == 0,
+              "the state is copied in words");
+constexpr int kCommitT = 256;
+
+__global__ __launch_bounds__(kCommitT) void k_search_commit(SearchState* __restrict__ Sp,
+                                                            const double* __restrict__ res,
+                                                            const int32_t* __restrict__ chains,
+                                                            int32_t m,
+                                                            int32_t* __restrict__ pchains,
+                                                            int32_t gate,
+                                                            SearchPeek* __restrict__ peek_out) {
     __shared__ double2 tab[kLog2Size];
+    __shared__ SearchState S;
     __shared__ int32_t slot[kMaxLambdas], slot_t[kMaxLambdas];
-    SearchState& S = *Sp;
-    if (gate && !S.run) return;  // uniform: the solve before this was skipped
+    if (gate && !Sp->run) return;  // uniform: the solve before this was skipped
+    const uint32_t* from = reinterpret_cast<const uint32_t*>(Sp);
+    uint32_t* to = reinterpret_cast<uint32_t*>(&S);
+    const int32_t n0 = min(max(Sp->npts, 0), kSearchMaxPts);
+    const int words = kHeadWords + n0 * kPtWords;
+    for (int x = threadIdx.x; x < words; x += kCommitT) to[x] = from[x];
     load_log2_table(tab);
+    __syncthreads();
     if (threadIdx.x == 0) {
         // points for todo[nin .. nin+m), in query order
         for (int g = 0; g < m; g++) {
@@ -268,23 +288,25 @@ __global__ __launch_bounds__(64) void k_search_commit(SearchState* __restrict__ 
             S.nsol++;
         }
         S.nin += m;
-    }
-    __syncthreads();
-    if (S.has_chain && chains && pchains) {
-        for (int g = 0; g < m; g++) {
-            const int at = slot[g];
-            if (at < 0) continue;
-            for (int r = threadIdx.x; r < slot_t[g] && r < S.s; r += blockDim.x)
-                pchains[(int64_t)at * S.s + r] = chains[(int64_t)g * S.s + r];
-        }
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
         if (S.status == -5)
             finish(S);
         else if (S.nin >= S.ntodo)
             advance(S, tab);  // the pass's solves are all in
         peek(S);
+        if (peek_out) *peek_out = S.peek;
+    }
+    __syncthreads();
+    uint32_t* back = reinterpret_cast<uint32_t*>(Sp);
+    for (int x = threadIdx.x; x < kHeadWords; x += kCommitT) back[x] = to[x];
+    for (int x = words + threadIdx.x; x < kHeadWords + S.npts * kPtWords; x += kCommitT)
+        back[x] = to[x];
+    if (S.has_chain && chains && pchains) {
+        for (int g = 0; g < m; g++) {
+            const int at = slot[g];
+            if (at < 0) continue;
+            for (int r = threadIdx.x; r < slot_t[g] && r < S.s; r += kCommitT)
+                pchains[(int64_t)at * S.s + r] = chains[(int64_t)g * S.s + r];
+        }
     }
 }
 
@@ -297,8 +319,9 @@ hipError_t launch_search_begin(SearchState* S, const SearchParams& P, const doub
 }
 
 hipError_t launch_search_commit(SearchState* S, const double* res, const int32_t* chains,
-                                int32_t m, int32_t* pchains, int32_t gate, hipStream_t st) {
-    k_search_commit<<<1, 64, 0, st>>>(S, res, chains, m, pchains, gate);
+                                int32_t m, int32_t* pchains, int32_t gate, SearchPeek* peek_out,
+                                hipStream_t st) {
+    k_search_commit<<<1, kCommitT, 0, st>>>(S, res, chains, m, pchains, gate, peek_out);
     return hipGetLastError();
 }
 
