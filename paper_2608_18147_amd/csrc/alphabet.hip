@@ -9,7 +9,7 @@
 //            each operation rounded to nearest, p_0 = min X, p_{m-1} = max X;
 //   quantile p_k = the input value at rank floor(k (d - 1) / (m - 1)).
 // A point equal to its predecessor (or, for the uniform grid, an inner point
-// not below max X) is dropped.  One workgroup walks the grid in tiles of 1024 points,
+// not below max X) is dropped.  One workgroup walks the grid in tiles of 4096 points,
 // a tile-wide scan of the kept flags placing the survivors.
 #include "device.hpp"
 #include "launch.hpp"
@@ -19,31 +19,58 @@ namespace ecasq {
 namespace {
 
 constexpr int kAT = 1024;
+// Points of a thread, and the one before them.  Their binary searches go level by
+// level together: a search is a chain of about 20 loads, and one after another (and each
+// point's predecessor again) they took 97 us for 4096 points of 2^20 values.
+constexpr int kAP = 4;
+constexpr int kAN = kAP + 1;
 
-// Last index i with v[i] <= q (v ascending, v[0] <= q).
-__device__ __forceinline__ int64_t last_le(const double* v, int64_t n, double q) {
-    int64_t lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo + 1) / 2;
-        if (v[mid] <= q)
-            lo = mid;
-        else
-            hi = mid - 1;
+// For each q: the last index i with v[i] <= q (v ascending, v[0] <= q).
+__device__ __forceinline__ void last_le(const double* v, int64_t n, const double (&q)[kAN],
+                                        int64_t (&lo)[kAN]) {
+    int64_t hi[kAN];
+#pragma unroll
+    for (int u = 0; u < kAN; u++) {
+        lo[u] = 0;
+        hi[u] = n - 1;
     }
-    return lo;
+    for (int64_t w = n - 1; w > 0; w >>= 1) {
+        double x[kAN];
+#pragma unroll
+        for (int u = 0; u < kAN; u++) x[u] = v[lo[u] + (hi[u] - lo[u] + 1) / 2];
+#pragma unroll
+        for (int u = 0; u < kAN; u++) {
+            const int64_t mid = lo[u] + (hi[u] - lo[u] + 1) / 2;
+            if (lo[u] < hi[u]) {
+                if (x[u] <= q[u]) lo[u] = mid;
+                else hi[u] = mid - 1;
+            }
+        }
+    }
 }
 
-// First index i with N[i] > r (N ascending integer counts, N[n-1] > r).
-__device__ __forceinline__ int64_t first_gt(const double* N, int64_t n, double r) {
-    int64_t lo = 0, hi = n - 1;
-    while (lo < hi) {
-        const int64_t mid = lo + (hi - lo) / 2;
-        if (N[mid] > r)
-            hi = mid;
-        else
-            lo = mid + 1;
+// For each r: the first index i with N[i] > r (N ascending integer counts, N[n-1] > r).
+__device__ __forceinline__ void first_gt(const double* N, int64_t n, const double (&r)[kAN],
+                                         int64_t (&lo)[kAN]) {
+    int64_t hi[kAN];
+#pragma unroll
+    for (int u = 0; u < kAN; u++) {
+        lo[u] = 0;
+        hi[u] = n - 1;
     }
-    return lo;
+    for (int64_t w = n - 1; w > 0; w >>= 1) {
+        double x[kAN];
+#pragma unroll
+        for (int u = 0; u < kAN; u++) x[u] = N[lo[u] + (hi[u] - lo[u]) / 2];
+#pragma unroll
+        for (int u = 0; u < kAN; u++) {
+            const int64_t mid = lo[u] + (hi[u] - lo[u]) / 2;
+            if (lo[u] < hi[u]) {
+                if (x[u] > r[u]) hi[u] = mid;
+                else lo[u] = mid + 1;
+            }
+        }
+    }
 }
 
 struct AlphaArgs {
@@ -56,73 +83,83 @@ struct AlphaArgs {
     int64_t* count;                // number of grid points kept
 };
 
-// Grid point k: its value and the index of the last input value <= it.
-__device__ __forceinline__ void point(const AlphaArgs& a, int64_t k, double& q, int64_t& idx) {
+// Grid points k0, k0 + 1, ..: their values and the indices of the last input values
+// <= them (k clamped to the grid).
+__device__ __forceinline__ void points(const AlphaArgs& a, int64_t k0, double (&q)[kAN],
+                                       int64_t (&idx)[kAN]) {
     if (a.kind == 1) {
         const double lo = a.v[0], hi = a.v[a.px - 1];
-        if (k == 0) {
-            q = lo;
-            idx = 0;
-            return;
-        }
-        if (k == a.m - 1) {
-            q = hi;
-            idx = a.px - 1;
-            return;
-        }
         const double step = (hi - lo) / (double)(a.m - 1);
-        q = lo + (double)k * step;
-        idx = last_le(a.v, a.px, q);
+#pragma unroll
+        for (int u = 0; u < kAN; u++) {
+            const int64_t k = min(max<int64_t>(k0 + u, 0), a.m - 1);
+            q[u] = k == 0 ? lo : k == a.m - 1 ? hi : lo + (double)k * step;
+        }
+        last_le(a.v, a.px, q, idx);
     } else {
-        const int64_t r = (k * (a.d - 1)) / (a.m - 1);
-        idx = first_gt(a.N, a.px, (double)r);
-        q = a.v[idx];
+        double r[kAN];
+#pragma unroll
+        for (int u = 0; u < kAN; u++) {
+            const int64_t k = min(max<int64_t>(k0 + u, 0), a.m - 1);
+            r[u] = (double)((k * (a.d - 1)) / (a.m - 1));
+        }
+        first_gt(a.N, a.px, r, idx);
+#pragma unroll
+        for (int u = 0; u < kAN; u++) q[u] = a.v[idx[u]];
     }
 }
 
 __global__ __launch_bounds__(kAT) void k_alphabet(AlphaArgs a) {
-    __shared__ int32_t scan[kAT];
-    __shared__ int64_t base;
-    const int tid = threadIdx.x;
-    if (tid == 0) base = 0;
+    constexpr int W = kAT / 64;
+    __shared__ int32_t part[2][W];
+    const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
+    int64_t base = 0;
+    int odd = 0;
     const double hi = a.v[a.px - 1];
-    for (int64_t t0 = 0; t0 < a.m; t0 += kAT) {
-        const int64_t k = t0 + tid;
-        double q = 0.0;
-        int64_t idx = 0;
-        int32_t keep = 0;
-        if (k < a.m) {
-            point(a, k, q, idx);
-            if (k == 0 || (a.kind == 1 && k == a.m - 1)) {
-                keep = 1;
-            } else {
-                // the points rise with k, so the predecessor is the largest
-                // point kept so far or a repeat of it
-                double qp;
-                int64_t ip;
-                point(a, k - 1, qp, ip);
-                keep = a.kind == 1 ? (q > qp && q < hi) : (idx > ip);
+    for (int64_t t0 = 0; t0 < a.m; t0 += kAT * kAP, odd ^= 1) {
+        const int64_t k0 = t0 + (int64_t)kAP * tid;
+        double q[kAN];
+        int64_t idx[kAN];
+        points(a, k0 - 1, q, idx);
+        bool keep[kAP];
+        int32_t own = 0;
+#pragma unroll
+        for (int u = 0; u < kAP; u++) {
+            const int64_t k = k0 + u;
+            // the points rise with k, so the predecessor is the largest
+            // point kept so far or a repeat of it
+            keep[u] = k < a.m && (k == 0 || (a.kind == 1 && k == a.m - 1) ||
+                                  (a.kind == 1 ? q[u + 1] > q[u] && q[u + 1] < hi
+                                               : idx[u + 1] > idx[u]));
+            own += keep[u];
+        }
+        int32_t at = own;  // inclusive scan over the wavefront, then the wavefronts
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const int32_t y = __shfl_up(at, off);
+            if (lane >= off) at += y;
+        }
+        if (lane == 63) part[odd][wave] = at;
+        __syncthreads();
+        int32_t total = 0;
+#pragma unroll
+        for (int w = 0; w < W; w++) {
+            const int32_t y = part[odd][w];
+            at += w < wave ? y : 0;
+            total += y;
+        }
+        int64_t o = base + at - own;
+#pragma unroll
+        for (int u = 0; u < kAP; u++) {
+            if (keep[u]) {
+                a.gv[o] = q[u + 1];
+                a.gN[o] = a.N[idx[u + 1]];
+                a.gS[o] = a.S[idx[u + 1]];
+                a.gS2[o] = a.S2[idx[u + 1]];
+                o++;
             }
         }
-        // inclusive scan of the kept flags (Hillis-Steele)
-        scan[tid] = keep;
-        __syncthreads();
-        for (int off = 1; off < kAT; off <<= 1) {
-            const int32_t add = tid >= off ? scan[tid - off] : 0;
-            __syncthreads();
-            scan[tid] += add;
-            __syncthreads();
-        }
-        if (keep) {
-            const int64_t o = base + scan[tid] - 1;
-            a.gv[o] = q;
-            a.gN[o] = a.N[idx];
-            a.gS[o] = a.S[idx];
-            a.gS2[o] = a.S2[idx];
-        }
-        __syncthreads();
-        if (tid == 0) base += scan[kAT - 1];
-        __syncthreads();
+        base += total;
     }
     if (tid == 0) *a.count = base;
 }
