@@ -179,7 +179,7 @@ __global__ __launch_bounds__(64) void k_rans_freqs(const unsigned long long* __r
     }
 }
 
-// A lane per segment.  The state's chain is two compares, two selects, a
+// A lane per segment (some repeated).  The state's chain is two compares, two selects, a
 // shift, the product's high half, a shift and a multiply-add; the bytes given
 // off gather in 64 bits and leave four at a time.
 __global__ __launch_bounds__(kRT) void k_rans_encode(const uint8_t* __restrict__ sym, int64_t d,
@@ -190,8 +190,10 @@ __global__ __launch_bounds__(kRT) void k_rans_encode(const uint8_t* __restrict__
     st[threadIdx.x] = tab[threadIdx.x];
     __syncthreads();
     const int lane = threadIdx.x % 64;
-    const int64_t seg = ((int64_t)blockIdx.x * kRWaves + threadIdx.x / 64) * lanes + lane;
-    if (lane >= lanes || seg >= nseg) return;
+    const int64_t seg0 = ((int64_t)blockIdx.x * kRWaves + threadIdx.x / 64) * lanes;
+    if (seg0 >= nseg) return;
+    const int64_t seg = min(seg0 + lane % lanes, nseg - 1);
+    const bool own = lane < lanes;  // the others' stores would only repeat these
     const uint8_t* in = sym + seg * kRSeg;
     const int n = (int)min((int64_t)kRSeg, d - seg * kRSeg);
     uint8_t* reg = scratch + seg * kRSegCap;
@@ -203,7 +205,7 @@ __global__ __launch_bounds__(kRT) void k_rans_encode(const uint8_t* __restrict__
         if (cnt >= 32u) {
             cnt -= 32u;
             w -= 4;
-            *reinterpret_cast<uint32_t*>(reg + w) = (uint32_t)(acc >> cnt);
+            if (own) *reinterpret_cast<uint32_t*>(reg + w) = (uint32_t)(acc >> cnt);
         }
     };
     auto put = [&](uint32_t q) {
@@ -241,7 +243,7 @@ __global__ __launch_bounds__(kRT) void k_rans_encode(const uint8_t* __restrict__
     lens[seg] = (uint32_t)(kRSegCap - w);
 }
 
-// One segment per wavefront, in LDS: lane 0 codes it.  A step stores two bytes
+// One segment per wavefront, in LDS, coded by every lane alike.  A step stores two bytes
 // below w and moves w by those that count (later bytes overwrite the others), so
 // there is no branch in it; the table entries of the next 8 symbols are read
 // while 8 are coded.
@@ -273,7 +275,7 @@ __global__ __launch_bounds__(kRT) void k_rans_encode_staged(const uint8_t* __res
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     int w = (int)kRSegCap;
-    if (lane == 0) {
+    {
         uint8_t* out = so[wave];
         const uint8_t* si = sy[wave];
         uint32_t x = kRL;
@@ -510,8 +512,9 @@ __global__ __launch_bounds__(kRT) void k_rans_decode(const uint8_t* __restrict__
         if (tid == 0) atomicAdd(bad, 1u);
         return;
     }
-    const int64_t seg = ((int64_t)blockIdx.x * kRWaves + wave) * lanes + lane;
-    if (lane >= lanes || seg >= nseg) return;
+    const int64_t seg0 = ((int64_t)blockIdx.x * kRWaves + wave) * lanes;
+    if (seg0 >= nseg) return;
+    const int64_t seg = min(seg0 + lane % lanes, nseg - 1);
     int64_t pos, hi;
     uint32_t x;
     int q0;
@@ -579,15 +582,15 @@ __global__ __launch_bounds__(kRT) void k_rans_decode(const uint8_t* __restrict__
             const uint32_t q = step();
             o[k / 4] = k % 4 == 0 ? q : o[k / 4] | (q << (8 * (k % 4)));
         }
-        __builtin_memcpy(out + i, o, 16);
+        if (lane < lanes) __builtin_memcpy(out + i, o, 16);
     }
     refill();
     for (; i < n; i++) out[i] = (uint8_t)step();
     if (x != kRL || pos + (int64_t)rd != hi) atomicAdd(bad, 1u);
 }
 
-// One segment per wavefront, in LDS (entries of 8 slots leave room for it): lane 0
-// decodes.  From its first state on a segment takes at most two bytes a symbol.
+// One segment per wavefront, in LDS (entries of 8 slots leave room for it), decoded
+// by every lane alike.  From its first state on a segment takes at most two bytes a symbol.
 constexpr int kDSegCap = 2 * kRSeg;
 
 __global__ __launch_bounds__(kRT) void k_rans_decode_staged(const uint8_t* __restrict__ in,
@@ -626,7 +629,7 @@ __global__ __launch_bounds__(kRT) void k_rans_decode_staged(const uint8_t* __res
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
     const int n = (int)min((int64_t)kRSeg, d - seg * kRSeg);
-    if (lane == 0) {
+    {
         const uint8_t* src = si[wave];
         uint32_t* dst = reinterpret_cast<uint32_t*>(so[wave]);
         uint32_t rd = 0;
@@ -659,7 +662,7 @@ __global__ __launch_bounds__(kRT) void k_rans_decode_staged(const uint8_t* __res
             for (int k = 0; i + k < n; k++) o |= step() << (8 * k);
             dst[i / 4] = o;
         }
-        if (x != kRL || rd != (uint32_t)len) atomicAdd(bad, 1u);
+        if (lane == 0 && (x != kRL || rd != (uint32_t)len)) atomicAdd(bad, 1u);
     }
     __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
     __builtin_amdgcn_wave_barrier();
