@@ -17,6 +17,7 @@
 #include <cstdio>
 #include <cstddef>
 #include <cstring>
+#include <mutex>
 #include <vector>
 
 #include "../../include/ecasq.h"
@@ -25,6 +26,118 @@
 using namespace ecasq;
 
 namespace {
+
+// Device memory of a solve comes from a pool of the library's own, one per
+// device, that keeps up to kPoolKeep between calls (0.7% of the card) and gives
+// what is above it back when a call ends.  The device's default pool keeps
+// nothing: mapping and unmapping 136 MB took 0.4 ms of each call, and the 1.4 GB of an
+// optimal solve up to 20 ms.  Allocation and release are ordered by the
+// stream, so calls on several threads and streams share the pool; where it cannot
+// be made or is out of memory, what it keeps is given back and the default pool is used.
+constexpr uint64_t kPoolKeep = (uint64_t)2 << 30;
+
+hipMemPool_t solve_pool(int dev) {
+    constexpr int kMaxDev = 64;
+    static std::mutex mu;
+    static hipMemPool_t pool[kMaxDev] = {};
+    static bool done[kMaxDev] = {};
+    if (dev < 0 || dev >= kMaxDev) return nullptr;
+    std::lock_guard<std::mutex> lock(mu);
+    if (!done[dev]) {
+        done[dev] = true;
+        hipMemPoolProps props;
+        std::memset(&props, 0, sizeof props);
+        props.allocType = hipMemAllocationTypePinned;
+        props.location.type = hipMemLocationTypeDevice;
+        props.location.id = dev;
+        uint64_t keep = kPoolKeep;
+        hipMemPool_t p = nullptr;
+        if (hipMemPoolCreate(&p, &props) == hipSuccess) {
+            if (hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess)
+                pool[dev] = p;
+            else
+                (void)hipMemPoolDestroy(p);
+        }
+        (void)hipGetLastError();
+    }
+    return pool[dev];
+}
+
+hipError_t solve_alloc(void** p, size_t bytes, hipStream_t st) {
+    int dev = -1;
+    if (hipGetDevice(&dev) == hipSuccess) {
+        if (hipMemPool_t pool = solve_pool(dev)) {
+            if (hipMallocFromPoolAsync(p, bytes, pool, st) == hipSuccess) return hipSuccess;
+            (void)hipMemPoolTrimTo(pool, 0);
+        }
+    }
+    (void)hipGetLastError();
+    return hipMallocAsync(p, bytes, st);
+}
+
+// Pinned host memory and the search's two events for one call: what the host
+// reads back goes there (a copy to pageable memory is staged and waited for by
+// itself), and blocks are kept for the next calls, kHostKeep at most (pinning
+// and two events cost about 100 us).
+struct HostBlock {
+    static constexpr size_t kBytes = 1 << 16;
+    static constexpr size_t kPoll = 0, kSmall = 512, kState = 1024, kUp = 8192, kChains = 16384;
+    static constexpr int32_t kChainInts = (int32_t)((kBytes - kChains) / sizeof(int32_t));
+    char* mem = nullptr;
+    hipEvent_t ev[2] = {nullptr, nullptr};
+    int dev = -1;
+    template <class T>
+    T* at(size_t off) const {
+        return reinterpret_cast<T*>(mem + off);
+    }
+};
+constexpr size_t kHostKeep = 8;
+std::mutex g_host_mu;
+std::vector<HostBlock> g_host_free;
+
+void host_destroy(HostBlock& b) {
+    for (auto& e : b.ev)
+        if (e) (void)hipEventDestroy(e);
+    if (b.mem) (void)hipHostFree(b.mem);
+    b = HostBlock();
+}
+
+bool host_acquire(HostBlock& b) {
+    int dev = -1;
+    if (hipGetDevice(&dev) != hipSuccess) return false;
+    {
+        std::lock_guard<std::mutex> lock(g_host_mu);
+        for (size_t k = 0; k < g_host_free.size(); k++)
+            if (g_host_free[k].dev == dev) {
+                b = g_host_free[k];
+                g_host_free.erase(g_host_free.begin() + (std::ptrdiff_t)k);
+                return true;
+            }
+    }
+    b.dev = dev;
+    void* h = nullptr;
+    bool ok = hipHostMalloc(&h, HostBlock::kBytes, hipHostMallocDefault) == hipSuccess;
+    if (ok) b.mem = static_cast<char*>(h);
+    for (auto& e : b.ev) {
+        ok = ok && hipEventCreateWithFlags(&e, hipEventDisableTiming) == hipSuccess;
+        if (!ok) e = nullptr;
+    }
+    if (!ok) host_destroy(b);
+    return ok;
+}
+
+// Once the stream has been waited for.
+void host_release(HostBlock& b) {
+    if (!b.mem) return;
+    {
+        std::lock_guard<std::mutex> lock(g_host_mu);
+        if (g_host_free.size() < kHostKeep) {
+            g_host_free.push_back(b);
+            b = HostBlock();
+        }
+    }
+    if (b.mem) host_destroy(b);
+}
 
 // Inspection log (ecasq_inspect_*): every DP solve's point of the budget
 // searches and every budget result's codebook before and after refinement.
@@ -150,8 +263,7 @@ struct Ctx {
     int32_t objective = 0;
     int32_t opt_full = 0;   // optimal DP: scan every predecessor
     int32_t refine_rounds = 0, refine_exhaustive = 0, recovery = 0;
-    SearchPeek* poll = nullptr;  // pinned host memory (device-resident search)
-    hipEvent_t ev[2] = {nullptr, nullptr};
+    HostBlock host;
 
     template <class T>
     T* at(size_t off) const {
@@ -180,23 +292,21 @@ ecasq_status ctx_open(Ctx& c, int64_t d, int32_t s, int32_t flags, void* stream,
         c.base = static_cast<char*>(ws);
     } else {
         void* p = nullptr;
-        if (hipMallocAsync(&p, c.L.total, c.st) != hipSuccess) return ECASQ_ENOMEM;
+        if (solve_alloc(&p, c.L.total, c.st) != hipSuccess) return ECASQ_ENOMEM;
         c.base = static_cast<char*>(p);
+    }
+    if (!host_acquire(c.host)) {
+        if (c.own) (void)hipFreeAsync(c.base, c.st);
+        c.base = nullptr;
+        return ECASQ_ENOMEM;
     }
     return ECASQ_OK;
 }
 
 void ctx_close(Ctx& c) {
-    if (c.poll || c.ev[0] || c.ev[1]) (void)hipStreamSynchronize(c.st);
-    for (auto& e : c.ev)
-        if (e) (void)hipEventDestroy(e);
-    if (c.poll) (void)hipHostFree(c.poll);
-    c.poll = nullptr;
-    c.ev[0] = c.ev[1] = nullptr;
-    if (c.own && c.base) {
-        (void)hipFreeAsync(c.base, c.st);
-        (void)hipStreamSynchronize(c.st);
-    }
+    if (c.own && c.base) (void)hipFreeAsync(c.base, c.st);
+    (void)hipStreamSynchronize(c.st);
+    host_release(c.host);
     c.base = nullptr;
 }
 
@@ -212,8 +322,8 @@ ecasq_status ctx_prep(Ctx& c, const void* x, int dt, int32_t alphabet = 0, int64
                         flags));
     // p, the non-finite flag, then S2[p-1] and N[0] (written by the last
     // preparation kernel as doubles): one read
-    int64_t hs[4] = {0, 0, 0, 0};
-    HIP_TRY(hipMemcpyAsync(hs, small, sizeof hs, hipMemcpyDeviceToHost, c.st));
+    int64_t* hs = c.host.at<int64_t>(HostBlock::kSmall);
+    HIP_TRY(hipMemcpyAsync(hs, small, sizeof(int64_t) * 4, hipMemcpyDeviceToHost, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));
     if ((uint32_t)hs[1] & 1u) return ECASQ_ENONFINITE;
     c.p = hs[0];
@@ -229,18 +339,19 @@ ecasq_status ctx_prep(Ctx& c, const void* x, int dt, int32_t alphabet = 0, int64
         HIP_TRY(launch_alphabet(alphabet, m, c.d, c.H.v, c.H.N, c.H.S, c.H.S2, c.p,
                                 c.at<double>(c.L.gv), c.at<double>(c.L.gN), c.at<double>(c.L.gS),
                                 c.at<double>(c.L.gS2), count, c.st));
-        int64_t np = 0;
-        HIP_TRY(hipMemcpyAsync(&np, count, sizeof np, hipMemcpyDeviceToHost, c.st));
+        // the grid's size and first count
+        HIP_TRY(hipMemcpyAsync(hs, count, sizeof(int64_t), hipMemcpyDeviceToHost, c.st));
+        HIP_TRY(hipMemcpyAsync(hs + 1, c.at<double>(c.L.gN), sizeof(double),
+                               hipMemcpyDeviceToHost, c.st));
         HIP_TRY(hipStreamSynchronize(c.st));
+        const int64_t np = hs[0];
         if (np < 2 || np > m) return ECASQ_EHIP;
         c.p = np;
         c.H.v = c.at<double>(c.L.gv);
         c.H.N = c.at<double>(c.L.gN);
         c.H.S = c.at<double>(c.L.gS);
         c.H.S2 = c.at<double>(c.L.gS2);
-        // the grid's first count
-        HIP_TRY(hipMemcpyAsync(&c0, c.H.N, sizeof(double), hipMemcpyDeviceToHost, c.st));
-        HIP_TRY(hipStreamSynchronize(c.st));
+        std::memcpy(&c0, hs + 1, sizeof c0);
     }
     c.s2tot = s2;
     c.H.p = c.p;
@@ -325,21 +436,21 @@ ecasq_status sweep_solve(Ctx& c, double lam, int32_t exact_s, Point& out, double
             HIP_TRY(launch_sweep_accumulators(S, dump->M + (int64_t)m * ls * ds,
                                               dump->P + (int64_t)m * ls * ds, c.st));
     }
-    double r[4];
-    HIP_TRY(hipMemcpyAsync(r, res, sizeof r, hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
-    const int32_t t = (int32_t)r[3];
-    if (t < 2 || t > imax) return ECASQ_EHIP;
-    out.chain.assign(t, 0);
-    HIP_TRY(hipMemcpyAsync(out.chain.data(), ch, sizeof(int32_t) * t, hipMemcpyDeviceToHost,
-                           c.st));
+    double* r = c.host.at<double>(HostBlock::kSmall);
+    const int32_t* hc = c.host.at<int32_t>(HostBlock::kChains);
+    HIP_TRY(hipMemcpyAsync(r, res, sizeof(double) * 4, hipMemcpyDeviceToHost, c.st));
+    HIP_TRY(hipMemcpyAsync(c.host.at<int32_t>(HostBlock::kChains), ch, sizeof(int32_t) * imax,
+                           hipMemcpyDeviceToHost, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));
     timing_flush();
+    const int32_t t = (int32_t)r[3];
+    if (t < 2 || t > imax) return ECASQ_EHIP;
+    out.chain.assign(hc, hc + t);
     out.lam = lam;
     out.H = r[2];
     out.M = r[1] / c.s2tot;
     out.t = t;
-    if (J4) std::memcpy(J4, r, sizeof r);
+    if (J4) std::memcpy(J4, r, sizeof(double) * 4);
     c.cells += dp_cells(p, imax);
     c.solves++;
     return ECASQ_OK;
@@ -485,7 +596,7 @@ ecasq_status opt_solve(Ctx& c, double lam, int32_t exact_s, std::vector<int32_t>
     const int32_t imax = (int32_t)std::min<int64_t>(c.s, c.p);
     const size_t bytes = opt_workspace_bytes(c.p, imax, Ktrace != nullptr);
     void* mem = nullptr;
-    if (hipMallocAsync(&mem, bytes, c.st) != hipSuccess) return ECASQ_ENOMEM;
+    if (solve_alloc(&mem, bytes, c.st) != hipSuccess) return ECASQ_ENOMEM;
     int32_t* ch = c.at<int32_t>(c.L.chain);
     double* res = c.at<double>(c.L.mres);
     const hipError_t e = launch_opt(c.H, imax, exact_s, lam * c.s2tot, c.opt_full,
@@ -500,7 +611,8 @@ ecasq_status opt_solve(Ctx& c, double lam, int32_t exact_s, std::vector<int32_t>
     const int32_t t = (int32_t)r[1];
     if (t < 2 || t > imax) return ECASQ_EHIP;
     chain.resize(t);
-    HIP_TRY(hipMemcpy(chain.data(), ch, sizeof(int32_t) * t, hipMemcpyDeviceToHost));
+    HIP_TRY(hipMemcpyAsync(chain.data(), ch, sizeof(int32_t) * t, hipMemcpyDeviceToHost, c.st));
+    HIP_TRY(hipStreamSynchronize(c.st));
     *J = r[0];
     c.cells += opt_cells(c.p, imax, exact_s);
     c.solves += 1;
@@ -581,22 +693,23 @@ struct SearchResult {
     ecasq_status status;
 };
 
-// Per-context host resources of the device-resident search: a pinned poll
-// block and two events (created on first use, released by ctx_close).
-ecasq_status search_host_init(Ctx& c) {
-    if (c.poll) return ECASQ_OK;
-    void* h = nullptr;
-    HIP_TRY(hipHostMalloc(&h, 2 * sizeof(SearchPeek), hipHostMallocDefault));
-    c.poll = static_cast<SearchPeek*>(h);
-    for (auto& e : c.ev) HIP_TRY(hipEventCreateWithFlags(&e, hipEventDisableTiming));
-    return ECASQ_OK;
+// The search state's fields before its point list, read back in one copy.
+int32_t kept_chains(const Ctx& c) {
+    return std::min<int32_t>(HostBlock::kChainInts / c.s, kSearchMaxPts);
 }
 
-// The search state's fields before its point list, read back in one copy.
 ecasq_status read_state(Ctx& c, SearchState& h) {
     SearchState* S = c.at<SearchState>(c.L.sstate);
-    HIP_TRY(hipMemcpyAsync(&h, S, offsetof(SearchState, pts), hipMemcpyDeviceToHost, c.st));
+    static_assert(offsetof(SearchState, pts) <= HostBlock::kUp - HostBlock::kState,
+                  "the state's fields fit their place");
+    char* at = c.host.at<char>(HostBlock::kState);
+    HIP_TRY(hipMemcpyAsync(at, S, offsetof(SearchState, pts), hipMemcpyDeviceToHost, c.st));
+    // the first points' codebooks with it (point_chain)
+    HIP_TRY(hipMemcpyAsync(c.host.at<int32_t>(HostBlock::kChains), c.at<int32_t>(c.L.schains),
+                           sizeof(int32_t) * (size_t)(kept_chains(c) * c.s),
+                           hipMemcpyDeviceToHost, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));
+    std::memcpy(&h, at, offsetof(SearchState, pts));
     return ECASQ_OK;
 }
 
@@ -610,6 +723,12 @@ Point to_point(const SearchPt& q) {
 }
 
 ecasq_status point_chain(Ctx& c, int32_t at, Point& P) {
+    if (P.t < 0 || P.t > c.s) return ECASQ_EHIP;
+    if (at < kept_chains(c)) {  // read back with the state
+        const int32_t* row = c.host.at<int32_t>(HostBlock::kChains) + (int64_t)at * c.s;
+        P.chain.assign(row, row + P.t);
+        return ECASQ_OK;
+    }
     P.chain.assign(P.t, 0);
     HIP_TRY(hipMemcpyAsync(P.chain.data(), c.at<int32_t>(c.L.schains) + (int64_t)at * c.s,
                            sizeof(int32_t) * P.t, hipMemcpyDeviceToHost, c.st));
@@ -633,29 +752,30 @@ void print_point(int32_t n, const SearchPt& q) {
 // (the poll costs nothing next to them, a skipped solve's launches would).
 constexpr int64_t kAheadBlocks = 1024;
 
-ecasq_status search_device_loop(Ctx& c, int32_t exact_s, int32_t max_passes) {
-    ECASQ_TRY(search_host_init(c));
+ecasq_status search_device_loop(Ctx& c, int32_t exact_s, int32_t max_passes, bool keep) {
     SearchState* S = c.at<SearchState>(c.L.sstate);
     double* res = c.at<double>(c.L.res);
     int32_t* ch = c.at<int32_t>(c.L.swchain);
     int32_t* pch = c.at<int32_t>(c.L.schains);
-    // the search may end without a solve (every query cached)
-    HIP_TRY(hipMemcpyAsync(c.poll, &S->peek, sizeof(SearchPeek), hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
-    if (c.poll[0].done) return ECASQ_OK;
+    SearchPeek* poll = c.host.at<SearchPeek>(HostBlock::kPoll);
+    if (keep) {  // the search may end without a solve (every query cached)
+        HIP_TRY(hipMemcpyAsync(poll, &S->peek, sizeof(SearchPeek), hipMemcpyDeviceToHost, c.st));
+        HIP_TRY(hipStreamSynchronize(c.st));
+        if (poll[0].done) return ECASQ_OK;
+    }
     const int32_t limit = 2 * max_passes + 8;  // each solve adds a point to a finite search
     const int32_t ahead = (c.p + 63) / 64 < kAheadBlocks ? 1 : 0;
     int32_t n = 0;
     for (;;) {
         ECASQ_TRY(sweep_enqueue(c, &S->todo_lamp[0], &S->run, exact_s));
-        HIP_TRY(launch_search_commit(S, res, ch, 1, pch, 1, c.poll + (n & 1), c.st));
-        HIP_TRY(hipEventRecord(c.ev[n & 1], c.st));
+        HIP_TRY(launch_search_commit(S, res, ch, 1, pch, 1, poll + (n & 1), c.st));
+        HIP_TRY(hipEventRecord(c.host.ev[n & 1], c.st));
         n++;
         if (n > ahead) {
             // the solve `ahead` places back and its commit
             const int32_t k = (n - 1 - ahead) & 1;
-            HIP_TRY(hipEventSynchronize(c.ev[k]));
-            const SearchPeek& pk = c.poll[k];
+            HIP_TRY(hipEventSynchronize(c.host.ev[k]));
+            const SearchPeek& pk = poll[k];
             if (timing_verbose()) print_point(pk.nsol, pk.last);
             if (pk.done) break;  // a queued solve finds run = 0
         }
@@ -725,15 +845,17 @@ ecasq_status search_host_pass(Ctx& c, const SearchState& h, int32_t exact_s) {
 // earlier searches on this input solved (a budget sweep), reusing any of
 // their multipliers the search queries again.
 ecasq_status search(Ctx& c, double b, int32_t exact_s, int32_t max_passes, int32_t width,
-                    SearchResult& R, bool keep = false) {
+                    SearchResult& R, bool keep = false, bool want_A = false) {
     if (width != 1 && width != kMaxLambdas) return ECASQ_EINVAL;
     if (c.objective != 0) width = 1;
     SearchState* S = c.at<SearchState>(c.L.sstate);
     // the two-value codebook {v_0, v_{p-1}}: B when no point is feasible
     {
-        int32_t ends[2] = {0, (int32_t)(c.p - 1)};
+        int32_t* ends = c.host.at<int32_t>(HostBlock::kUp);
+        ends[0] = 0;
+        ends[1] = (int32_t)(c.p - 1);
         int32_t* ech = c.at<int32_t>(c.L.cchain);
-        HIP_TRY(hipMemcpyAsync(ech, ends, sizeof ends, hipMemcpyHostToDevice, c.st));
+        HIP_TRY(hipMemcpyAsync(ech, ends, sizeof(int32_t) * 2, hipMemcpyHostToDevice, c.st));
         HIP_TRY(launch_metrics(c.H, 2, ech, 0.0, c.s2tot, c.at<double>(c.L.two), c.st));
     }
     SearchParams P;
@@ -750,7 +872,7 @@ ecasq_status search(Ctx& c, double b, int32_t exact_s, int32_t max_passes, int32
     const int32_t solves0 = c.solves;
     SearchState h;
     if (c.objective == 0 && c.sweep && width == 1) {
-        ECASQ_TRY(search_device_loop(c, exact_s, max_passes));
+        ECASQ_TRY(search_device_loop(c, exact_s, max_passes, keep));
         ECASQ_TRY(read_state(c, h));
         const int32_t imax = (int32_t)std::min<int64_t>(c.s, c.p);
         c.solves += h.nsol;
@@ -786,7 +908,7 @@ ecasq_status search(Ctx& c, double b, int32_t exact_s, int32_t max_passes, int32
     R.have_A = h.have_A != 0;
     if (R.have_A) {
         R.A = to_point(h.A);
-        if (P.has_chain) ECASQ_TRY(point_chain(c, h.iA, R.A));
+        if (P.has_chain && want_A) ECASQ_TRY(point_chain(c, h.iA, R.A));
     }
     return ECASQ_OK;
 }
@@ -914,8 +1036,12 @@ ecasq_status finish(Ctx& c, std::vector<int32_t>& chain, double lam, double b, b
     const int32_t t = (int32_t)chain.size();
     int32_t* ch = c.at<int32_t>(c.L.chain);
     int32_t* stats = ch + c.s + 2;
-    HIP_TRY(hipMemcpyAsync(ch, chain.data(), sizeof(int32_t) * t, hipMemcpyHostToDevice, c.st));
-    HIP_TRY(hipMemsetAsync(stats, 0, sizeof(int32_t) * 2, c.st));
+    // the chain and, after it, the cleared counts of the refinement
+    int32_t* up = c.host.at<int32_t>(HostBlock::kUp);
+    std::memset(up, 0, sizeof(int32_t) * (size_t)(c.s + 4));
+    std::memcpy(up, chain.data(), sizeof(int32_t) * t);
+    HIP_TRY(hipMemcpyAsync(ch, up, sizeof(int32_t) * (size_t)(c.s + 4), hipMemcpyHostToDevice,
+                           c.st));
     if (o.refine_rounds > 0 && std::isfinite(lam) && t >= 3)
         HIP_TRY(launch_refine(c.H, t, ch, lam * c.s2tot, b, budget ? 1 : 0, o.refine_rounds,
                               o.refine_exhaustive, stats, c.st));
@@ -933,10 +1059,10 @@ ecasq_status finish(Ctx& c, std::vector<int32_t>& chain, double lam, double b, b
         HIP_TRY(hipStreamSynchronize(c.st));
         g_ins_res.push_back(std::move(r));
     }
-    double m[6];
-    int32_t stt[2];
-    HIP_TRY(hipMemcpyAsync(m, mres, sizeof m, hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipMemcpyAsync(stt, stats, sizeof stt, hipMemcpyDeviceToHost, c.st));
+    double* m = c.host.at<double>(HostBlock::kSmall);
+    int32_t* stt = c.host.at<int32_t>(HostBlock::kSmall + 256);
+    HIP_TRY(hipMemcpyAsync(m, mres, sizeof(double) * 6, hipMemcpyDeviceToHost, c.st));
+    HIP_TRY(hipMemcpyAsync(stt, stats, sizeof(int32_t) * 2, hipMemcpyDeviceToHost, c.st));
     HIP_TRY(hipStreamSynchronize(c.st));
     if (info) {
         std::memset(info, 0, sizeof *info);
@@ -1119,7 +1245,7 @@ ecasq_status solve_timeshare(const void* x, int dt, int64_t d, int32_t s, double
         cp = cm;
     } else {
         SearchResult R;
-        ECASQ_TRY(search(c, b, o.exact_s, o.max_search_passes, o.search_width, R));
+        ECASQ_TRY(search(c, b, o.exact_s, o.max_search_passes, o.search_width, R, false, true));
         status = R.status;
         passes = R.passes;
         lam_m = lam_p = R.B.lam;
@@ -1346,7 +1472,7 @@ ecasq_status ecasq_encode(const uint8_t* symbols, int64_t d, int32_t t, void* st
     if (capacity < rans_bound(d, t)) return ECASQ_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
     void* mem = nullptr;
-    if (hipMallocAsync(&mem, rans_scratch_bytes(d), st) != hipSuccess) return ECASQ_ENOMEM;
+    if (solve_alloc(&mem, rans_scratch_bytes(d), st) != hipSuccess) return ECASQ_ENOMEM;
     const RansResult* res = nullptr;
     RansResult got{};
     ecasq_status rc = ECASQ_OK;
