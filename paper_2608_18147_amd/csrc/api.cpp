@@ -316,10 +316,15 @@ void ctx_close(Ctx& c) {
 ecasq_status ctx_prep(Ctx& c, const void* x, int dt, int32_t alphabet = 0, int64_t m = 0) {
     int64_t* small = c.at<int64_t>(c.L.small);
     uint32_t* flags = reinterpret_cast<uint32_t*>(small + 1);
-    HIP_TRY(hipMemsetAsync(small, 0, sizeof(int64_t) * 8, c.st));
-    HIP_TRY(launch_prep(x, dt, c.d, c.base + c.L.prep, c.st, c.at<double>(c.L.v),
-                        c.at<double>(c.L.N), c.at<double>(c.L.S), c.at<double>(c.L.S2), small,
-                        flags));
+    if (prep_is_small(c.d)) {
+        HIP_TRY(launch_prep_small(x, dt, c.d, c.st, c.at<double>(c.L.v), c.at<double>(c.L.N),
+                                  c.at<double>(c.L.S), c.at<double>(c.L.S2), small));
+    } else {
+        HIP_TRY(hipMemsetAsync(small, 0, sizeof(int64_t) * 8, c.st));
+        HIP_TRY(launch_prep(x, dt, c.d, c.base + c.L.prep, c.st, c.at<double>(c.L.v),
+                            c.at<double>(c.L.N), c.at<double>(c.L.S), c.at<double>(c.L.S2),
+                            small, flags));
+    }
     // p, the non-finite flag, then S2[p-1] and N[0] (written by the last
     // preparation kernel as doubles): one read
     int64_t* hs = c.host.at<int64_t>(HostBlock::kSmall);

@@ -29,6 +29,12 @@ size_t prep_scratch_bytes(int64_t d);
 hipError_t launch_prep(const void* x, int dt, int64_t d, void* scratch, hipStream_t st, double* v,
                        double* N, double* S, double* S2, int64_t* p_dev, uint32_t* flags_dev);
 
+// The same in one launch for d with prep_is_small(d); out: p, 1 if an entry is not
+// finite, then S2[p-1] and N[0] as doubles.
+bool prep_is_small(int64_t d);
+hipError_t launch_prep_small(const void* x, int dt, int64_t d, hipStream_t st, double* v,
+                             double* N, double* S, double* S2, int64_t* out);
+
 // ---- alphabet.hip ----
 // kind 1: uniform grid of m points over [v[0], v[px-1]]; kind 2: the input
 // values at ranks floor(k (d-1) / (m-1)); repeats dropped.  Writes the grid and

@@ -293,6 +293,134 @@ __global__ __launch_bounds__(kScanBlock) void k_scan_emit(const uint32_t* __rest
     }
 }
 
+// The whole preparation of a small input in one workgroup and one launch: keys
+// and a bitonic sort in LDS, E entries per thread, the scan of the threads' exact
+// sums and the histogram.  The 18 launches of the general path take 110 us for
+// 1024 entries (E = 1), most of it in their starts and in single wavefronts.
+constexpr int kPT = 1024;
+
+template <int DT>
+__device__ __forceinline__ uint32_t bits_of(const void* __restrict__ x, int64_t i) {
+    if (DT == 0) return reinterpret_cast<const uint32_t*>(x)[i];
+    if (DT == 1) return __float_as_uint(__half2float(reinterpret_cast<const __half*>(x)[i]));
+    return ((uint32_t)reinterpret_cast<const uint16_t*>(x)[i]) << 16;
+}
+
+template <int DT, int E>
+__global__ __launch_bounds__(kPT) void k_prep_small(const void* __restrict__ x, int32_t d,
+                                                    double* __restrict__ v,
+                                                    double* __restrict__ N,
+                                                    double* __restrict__ S,
+                                                    double* __restrict__ S2,
+                                                    int64_t* __restrict__ out) {
+    __shared__ uint32_t key[kPT * E];
+    __shared__ uint64_t part[kPT][kRec + 1];  // padded: lanes spread over the banks
+    const int tid = threadIdx.x;
+    bool bad = false;
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const int i = tid + kPT * e;
+        uint32_t k = 0xFFFFFFFFu;  // above every key of a finite value
+        if (i < d) {
+            uint32_t bits = bits_of<DT>(x, i);
+            if ((bits & 0x7F800000u) == 0x7F800000u) {
+                bad = true;
+                bits = 0u;
+            }
+            k = f32_key(bits);
+        }
+        key[i] = k;
+    }
+    const int any_bad = __syncthreads_or(bad);
+    int n2 = 2;
+    while (n2 < d) n2 <<= 1;
+    for (int k = 2; k <= n2; k <<= 1) {
+        for (int j = k >> 1; j > 0; j >>= 1) {
+            for (int y = tid; y < n2 / 2; y += kPT) {
+                const int i = 2 * y - (y & (j - 1));
+                const uint32_t a = key[i], b = key[i + j];
+                if ((a > b) == ((i & k) == 0)) {
+                    key[i] = b;
+                    key[i + j] = a;
+                }
+            }
+            __syncthreads();
+        }
+    }
+    uint32_t kk[E + 1];
+#pragma unroll
+    for (int e = 0; e <= E; e++) {
+        const int i = E * tid + e;
+        kk[e] = i < d ? key[i] : 0xFFFFFFFFu;
+    }
+    uint64_t r[kRec];
+    {
+        uint64_t s[kSL] = {0}, q[kS2L] = {0}, ends = 0;
+#pragma unroll
+        for (int e = 0; e < E; e++) {
+            if (E * tid + e < d) {
+                accumulate(s, q, term_of(key_bits(kk[e])));
+                ends += kk[e + 1] != kk[e];
+            }
+        }
+#pragma unroll
+        for (int l = 0; l < kSL; l++) r[l] = s[l];
+#pragma unroll
+        for (int l = 0; l < kS2L; l++) r[kSL + l] = q[l];
+        r[kRec - 1] = ends;
+    }
+#pragma unroll
+    for (int l = 0; l < kRec; l++) part[tid][l] = r[l];
+    __syncthreads();
+    const int used = (d + E - 1) / E;  // threads that have entries
+    for (int off = 1; off < used; off <<= 1) {
+        uint64_t t[kRec];
+        const bool on = tid >= off && tid < used;
+        if (on) {
+#pragma unroll
+            for (int l = 0; l < kRec; l++) t[l] = part[tid - off][l];
+        }
+        __syncthreads();
+        if (on) {
+            rec_add(r, t);
+#pragma unroll
+            for (int l = 0; l < kRec; l++) part[tid][l] = r[l];
+        }
+        __syncthreads();
+    }
+    if (tid == 0) out[1] = any_bad ? 1 : 0;
+    if (tid >= used) return;
+    uint64_t s[kSL] = {0}, q[kS2L] = {0};
+    int64_t u = 0;
+    if (tid > 0) {
+#pragma unroll
+        for (int l = 0; l < kSL; l++) s[l] = part[tid - 1][l];
+#pragma unroll
+        for (int l = 0; l < kS2L; l++) q[l] = part[tid - 1][kSL + l];
+        u = (int64_t)part[tid - 1][kRec - 1];
+    }
+#pragma unroll
+    for (int e = 0; e < E; e++) {
+        const int i = E * tid + e;
+        if (i >= d) break;
+        const uint32_t bits = key_bits(kk[e]);
+        accumulate(s, q, term_of(bits));
+        if (kk[e + 1] == kk[e]) continue;
+        const double s2 = wide_to_double<kS2L>(q, false, -298);
+        v[u] = (double)__uint_as_float(bits);
+        N[u] = (double)(i + 1);
+        S[u] = wide_to_double<kSL>(s, true, -149);
+        S2[u] = s2;
+        double* o = reinterpret_cast<double*>(out);
+        if (u == 0) o[3] = (double)(i + 1);
+        if (i == d - 1) {
+            out[0] = u + 1;
+            o[2] = s2;
+        }
+        u++;
+    }
+}
+
 // ||X||^2 = S2[p-1] and the count of the smallest value N[0] beside p in
 // the host-read slots (one read after preparation instead of two).
 __global__ void k_prep_tail(const int64_t* __restrict__ p, const double* __restrict__ N,
@@ -315,6 +443,24 @@ size_t prep_scratch_bytes(int64_t d) {
     b += align256(sizeof(uint64_t) * kRec * ((nchunk + kScanBlock - 1) / kScanBlock));  // runs
     b += align256(sizeof(uint32_t) * 4);               // flags
     return b;
+}
+
+bool prep_is_small(int64_t d) { return d <= 4 * kPT; }
+
+hipError_t launch_prep_small(const void* x, int dt, int64_t d, hipStream_t st, double* v,
+                             double* N, double* S, double* S2, int64_t* out) {
+    if (d < 1 || !prep_is_small(d)) return hipErrorInvalidValue;
+    const int32_t n = (int32_t)d;
+    if (d <= kPT) {
+        if (dt == 0) k_prep_small<0, 1><<<1, kPT, 0, st>>>(x, n, v, N, S, S2, out);
+        else if (dt == 1) k_prep_small<1, 1><<<1, kPT, 0, st>>>(x, n, v, N, S, S2, out);
+        else k_prep_small<2, 1><<<1, kPT, 0, st>>>(x, n, v, N, S, S2, out);
+    } else {
+        if (dt == 0) k_prep_small<0, 4><<<1, kPT, 0, st>>>(x, n, v, N, S, S2, out);
+        else if (dt == 1) k_prep_small<1, 4><<<1, kPT, 0, st>>>(x, n, v, N, S, S2, out);
+        else k_prep_small<2, 4><<<1, kPT, 0, st>>>(x, n, v, N, S, S2, out);
+    }
+    return hipGetLastError();
 }
 
 hipError_t launch_prep(const void* x, int dt, int64_t d, void* scratch, hipStream_t st, double* v,
