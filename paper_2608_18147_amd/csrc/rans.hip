@@ -94,15 +94,21 @@ __global__ __launch_bounds__(256) void k_sym_hist(const uint8_t* __restrict__ sy
 // in [1, 2^l]).  f = 1 would need m = 2^32 + 1: there m = 2^32 - 1 and s = 0
 // give x - 1 (x >= 1), and the bias makes up for it.
 struct EncSym {
-    uint32_t xmax;  // 2^15 f: x at or above gives off a byte first
+    uint32_t xtop;  // 2^15 f - 1: x above gives off a byte first
     uint32_t m;
     uint32_t bias;
     uint32_t cs;    // 2^16 - f, s in the top byte
 };
 
+// Bits that state x gives off before the symbol: a byte if x > xtop, two if x / 2^8
+// is (x < 2^31: at most two), from the differences' signs.
+__device__ __forceinline__ uint32_t bits_off(uint32_t x, uint32_t xtop) {
+    return (((xtop - x) >> 31) + ((xtop - (x >> 8)) >> 31)) << 3;
+}
+
 __device__ __forceinline__ EncSym enc_sym(uint32_t f, uint32_t c) {
     EncSym e;
-    e.xmax = f << 15;
+    e.xtop = (f << 15) - 1u;
     if (f == 1u) {
         e.m = 0xFFFFFFFFu;
         e.bias = c + kRM - 1u;
@@ -210,8 +216,7 @@ __global__ __launch_bounds__(kRT) void k_rans_encode(const uint8_t* __restrict__
     };
     auto put = [&](uint32_t q) {
         const EncSym e = st[q];
-        // x < 2^31: at most two bytes
-        const uint32_t sh = (x >> 8) >= e.xmax ? 16u : x >= e.xmax ? 8u : 0u;
+        const uint32_t sh = bits_off(x, e.xtop);
         const uint32_t two = __builtin_amdgcn_perm(0u, x, 0x0c0c0001u);  // low two bytes, swapped
         acc = (acc << sh) | (two >> (16u - sh));
         cnt += sh;
@@ -280,12 +285,11 @@ __global__ __launch_bounds__(kRT) void k_rans_encode_staged(const uint8_t* __res
         const uint8_t* si = sy[wave];
         uint32_t x = kRL;
         auto put = [&](const EncSym& e) {
-            // x < 2^31: at most two bytes
-            const bool n2 = (x >> 8) >= e.xmax, n1 = x >= e.xmax;
+            const uint32_t sh = bits_off(x, e.xtop);
             out[w - 1] = (uint8_t)x;
             out[w - 2] = (uint8_t)(x >> 8);
-            w -= n2 ? 2 : n1 ? 1 : 0;
-            x >>= n2 ? 16 : n1 ? 8 : 0;
+            w -= (int)(sh >> 3);
+            x >>= sh;
             const uint32_t k = __umulhi(e.m, x) >> (e.cs >> 24);
             x = x + e.bias + __umul24(k, e.cs & 0xFFFFu);
         };
@@ -485,12 +489,15 @@ __device__ __forceinline__ bool first_state(const DecBook<SL>& B, const uint8_t*
     return true;
 }
 
-// x after symbol q's bytes b0, b1; n: how many it took.
+// x after symbol q's bytes b0, b1 (y >= 2^7); n: how many it took, one below L =
+// 2^23 and two below 2^15, from the leading zeros: a select waits longer for its compare than
+// these shifts take.
 __device__ __forceinline__ uint32_t with_bytes(uint32_t y, uint32_t b0, uint32_t b1, uint32_t& n) {
-    const uint32_t y1 = (y << 8) | b0, y2 = (y1 << 8) | b1;
-    const bool n1 = y < kRL, n2 = y < (kRL >> 8);
-    n = n2 ? 2u : n1 ? 1u : 0u;
-    return n2 ? y2 : n1 ? y1 : y;
+    const uint32_t z = (uint32_t)__builtin_clz(y);
+    const uint32_t sh = __builtin_elementwise_sub_sat(z, 1u) & 24u;
+    n = sh >> 3;
+    const uint64_t w = ((uint64_t)y << 32) | (b0 << 24) | (b1 << 16);
+    return (uint32_t)((w << sh) >> 32);
 }
 
 // Many segments: one lane each, straight from and to memory.  An entry for every 4
