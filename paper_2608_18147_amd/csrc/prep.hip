@@ -482,8 +482,10 @@ hipError_t launch_prep(const void* x, int dt, int64_t d, void* scratch, hipStrea
     if (dt == 0) k_ingest<0><<<ig, 256, 0, st>>>(x, d, k0, flags_dev);
     else if (dt == 1) k_ingest<1><<<ig, 256, 0, st>>>(x, d, k0, flags_dev);
     else k_ingest<2><<<ig, 256, 0, st>>>(x, d, k0, flags_dev);
-    for (int pass = 0; pass < 4; pass++) {
-        const int shift = 8 * pass;
+    // A 16-bit type's keys differ in their upper bits alone (bf16: 16; f16: 19, whose
+    // subnormals have no more mantissa bits than the rest): the lower ones are
+    // all zeros or, below zero, all ones, so two or three passes sort them.
+    for (int shift = dt == 0 ? 0 : dt == 1 ? 13 : 16; shift < 32; shift += 8) {
         k_radix_hist<<<(unsigned)nblk, kSortBlock, 0, st>>>(k0, d, shift, hist, (int)nblk);
         k_scan_u32<<<1, 1024, 0, st>>>(hist, 256 * nblk);
         k_radix_scatter<<<(unsigned)nblk, kSortBlock, 0, st>>>(k0, k1, d, shift, hist, (int)nblk);
