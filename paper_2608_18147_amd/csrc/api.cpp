@@ -1525,13 +1525,10 @@ ecasq_status ecasq_quantize(const void* x, ecasq_dtype dt, int64_t d, const doub
         return ECASQ_OK;
     }
     void* h = nullptr;
-    if (hipMallocAsync(&h, sizeof(unsigned long long) * 256, st) != hipSuccess)
-        return ECASQ_ENOMEM;
-    unsigned long long* hh = static_cast<unsigned long long*>(h);
+    if (hipMallocAsync(&h, quantize_scratch_bytes(d), st) != hipSuccess) return ECASQ_ENOMEM;
     ecasq_status rc = ECASQ_OK;
-    if (hipMemsetAsync(hh, 0, sizeof(unsigned long long) * 256, st) != hipSuccess ||
-        launch_quantize(x, dt, d, codebook, t, seed, symbols, hh, st) != hipSuccess ||
-        launch_entropy(hh, t, d, empirical_entropy, hist, st) != hipSuccess)
+    if (launch_quantize_scratch(x, dt, d, codebook, t, seed, symbols, empirical_entropy, hist, h,
+                                st) != hipSuccess)
         rc = ECASQ_EHIP;
     if (hipFreeAsync(h, st) != hipSuccess) rc = ECASQ_EHIP;
     return rc;

@@ -247,6 +247,12 @@ bool quantize_is_small(int64_t d);
 hipError_t launch_quantize_small(const void* x, int dt, int64_t d, const double* codebook,
                                  int32_t t, uint64_t seed, uint8_t* symbols, double* ent,
                                  int64_t* hist_out, hipStream_t st);
+// rounding and entropy with quantize_scratch_bytes(d) of memory, which need not be
+// cleared
+size_t quantize_scratch_bytes(int64_t d);
+hipError_t launch_quantize_scratch(const void* x, int dt, int64_t d, const double* codebook,
+                                   int32_t t, uint64_t seed, uint8_t* symbols, double* ent,
+                                   int64_t* hist_out, void* scratch, hipStream_t st);
 // the allocation-free rounding's counts: a file-scope device array of 256
 // entries, its address on the current device (looked up once per device)
 hipError_t quantize_scratch(unsigned long long** out);

@@ -431,12 +431,15 @@ __device__ __forceinline__ unsigned int fold_copies(const unsigned int* __restri
     return n;
 }
 
-template <int DT>
+// PARTS: each workgroup's counts in a row of its own, 256 words (nothing to
+// clear before); otherwise added to hist.
+template <int DT, bool PARTS>
 __global__ __launch_bounds__(kQT) void k_quantize(const void* __restrict__ x, int64_t d,
                                                   const double* __restrict__ cb, int32_t t,
                                                   uint32_t k0, uint32_t k1,
                                                   uint8_t* __restrict__ symbols,
-                                                  unsigned long long* __restrict__ hist) {
+                                                  unsigned long long* __restrict__ hist,
+                                                  uint32_t* __restrict__ parts) {
     __shared__ RoundBook B;
     __shared__ unsigned int lh[kQCopies * kQPad];
     for (int r = threadIdx.x; r < kQCopies * kQPad; r += kQT) lh[r] = 0u;
@@ -446,7 +449,10 @@ __global__ __launch_bounds__(kQT) void k_quantize(const void* __restrict__ x, in
     __syncthreads();
     if ((int)threadIdx.x < t) {
         const unsigned int n = fold_copies(lh, threadIdx.x);
-        if (n) atomicAdd(&hist[threadIdx.x], (unsigned long long)n);
+        if constexpr (PARTS)
+            parts[(int64_t)blockIdx.x * kMaxT + threadIdx.x] = n;
+        else if (n)
+            atomicAdd(&hist[threadIdx.x], (unsigned long long)n);
     }
 }
 
@@ -573,6 +579,36 @@ __global__ __launch_bounds__(256) void k_entropy(const unsigned long long* __res
     if (threadIdx.x == 0) *ent = H;
 }
 
+// The same from the rows of n workgroups (d < 2^32 entries in all).
+__global__ __launch_bounds__(kQT) void k_entropy_parts(const uint32_t* __restrict__ parts,
+                                                       int32_t n, int32_t t, int64_t d,
+                                                       double* __restrict__ ent,
+                                                       int64_t* __restrict__ hist_out) {
+    constexpr int G = kQT / kMaxT;
+    __shared__ double2 tab[kLog2Size];
+    __shared__ double red[4];
+    __shared__ uint32_t sum[G][kMaxT];
+    __shared__ unsigned long long hist[kMaxT];
+    load_log2_table(tab);
+    const int r = threadIdx.x % kMaxT, g = threadIdx.x / kMaxT;
+    uint32_t c = 0;
+    if (r < t) {
+#pragma unroll 8
+        for (int32_t b = g; b < n; b += G) c += parts[(int64_t)b * kMaxT + r];
+    }
+    sum[g][r] = c;
+    __syncthreads();
+    if (g == 0) {
+        uint32_t a = 0;
+#pragma unroll
+        for (int k = 0; k < G; k++) a += sum[k][r];
+        hist[r] = a;
+    }
+    __syncthreads();
+    const double H = plugin_entropy(hist, t, (double)d, hist_out, tab, red);
+    if (threadIdx.x == 0) *ent = H;
+}
+
 // Rounding and entropy of a small input in one launch of one workgroup: no
 // counts in memory, nothing to clear, no second kernel.
 template <int DT>
@@ -659,9 +695,10 @@ hipError_t launch_gather(const double* v, const int32_t* u, int32_t t, double* c
     return hipGetLastError();
 }
 
-// One workgroup up to here (16 entries per thread): d = 4096 takes 15 us less
-// than with a cleared count array, a second kernel and the array's allocation.
-constexpr int64_t kQSmall = 16 * kQT;
+// One workgroup up to here: a call of 4096 entries takes 14 us, one more launch,
+// the counts' allocation and its release 26 us more whatever the size, and the
+// one workgroup about 7 us for every 16384 entries.
+constexpr int64_t kQSmall = 32 * kQT;
 
 bool quantize_is_small(int64_t d) { return d <= kQSmall; }
 
@@ -679,19 +716,57 @@ hipError_t launch_quantize_small(const void* x, int dt, int64_t d, const double*
     return hipGetLastError();
 }
 
+// Rows of counts up to here (one launch less to clear a count array, and up to 256
+// rows are summed in about 5 us); above, the workgroups are twice as many
+// and their time is what counts.
+constexpr int64_t kQParts = (int64_t)1 << 22;
+
+size_t quantize_scratch_bytes(int64_t d) {
+    return d <= kQParts ? sizeof(uint32_t) * kMaxT * 256 : sizeof(unsigned long long) * kMaxT;
+}
+
+namespace {
+
+template <bool PARTS>
+void quantize_groups(const void* x, int dt, int64_t d, const double* codebook, int32_t t,
+                     uint64_t seed, uint8_t* symbols, unsigned long long* hist, uint32_t* parts,
+                     unsigned g, hipStream_t st) {
+    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
+    if (dt == 0)
+        k_quantize<0, PARTS><<<g, kQT, 0, st>>>(x, d, codebook, t, k0, k1, symbols, hist, parts);
+    else if (dt == 1)
+        k_quantize<1, PARTS><<<g, kQT, 0, st>>>(x, d, codebook, t, k0, k1, symbols, hist, parts);
+    else
+        k_quantize<2, PARTS><<<g, kQT, 0, st>>>(x, d, codebook, t, k0, k1, symbols, hist, parts);
+}
+
+}  // namespace
+
 hipError_t launch_quantize(const void* x, int dt, int64_t d, const double* codebook, int32_t t,
                            uint64_t seed, uint8_t* symbols, unsigned long long* hist,
                            hipStream_t st) {
     // 8 entries per thread at least, two workgroups (all wavefronts) per CU at most
     int64_t g = (d + 8 * kQT - 1) / (8 * kQT);
     if (g > 512) g = 512;
-    const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
-    if (dt == 0)
-        k_quantize<0><<<(unsigned)g, kQT, 0, st>>>(x, d, codebook, t, k0, k1, symbols, hist);
-    else if (dt == 1)
-        k_quantize<1><<<(unsigned)g, kQT, 0, st>>>(x, d, codebook, t, k0, k1, symbols, hist);
-    else
-        k_quantize<2><<<(unsigned)g, kQT, 0, st>>>(x, d, codebook, t, k0, k1, symbols, hist);
+    quantize_groups<false>(x, dt, d, codebook, t, seed, symbols, hist, nullptr, (unsigned)g, st);
+    return hipGetLastError();
+}
+
+hipError_t launch_quantize_scratch(const void* x, int dt, int64_t d, const double* codebook,
+                                   int32_t t, uint64_t seed, uint8_t* symbols, double* ent,
+                                   int64_t* hist_out, void* scratch, hipStream_t st) {
+    if (d > kQParts) {
+        auto* hist = static_cast<unsigned long long*>(scratch);
+        hipError_t e = hipMemsetAsync(hist, 0, sizeof(unsigned long long) * kMaxT, st);
+        if (e == hipSuccess)
+            e = launch_quantize(x, dt, d, codebook, t, seed, symbols, hist, st);
+        return e == hipSuccess ? launch_entropy(hist, t, d, ent, hist_out, st) : e;
+    }
+    auto* parts = static_cast<uint32_t*>(scratch);
+    int64_t g = (d + 8 * kQT - 1) / (8 * kQT);
+    if (g > 256) g = 256;
+    quantize_groups<true>(x, dt, d, codebook, t, seed, symbols, nullptr, parts, (unsigned)g, st);
+    k_entropy_parts<<<1, kQT, 0, st>>>(parts, (int32_t)g, t, d, ent, hist_out);
     return hipGetLastError();
 }
 
