@@ -19,14 +19,17 @@
 // word, and every later wait then ends at once.
 //
 // Columns per workgroup: 8 while that gives at most 256 workgroups (p <= 2048);
-// above, 32 of the first 1024, 16 of the next 1024 and 8 beyond (32 costs in a thread
-// of each).
+// up to 3072, 32 of the first 1024, 16 of the next 1024 and 8 beyond (32 costs in a
+// thread of each).  Above, that would be up to 352 workgroups for 256 CUs, the last of
+// them after the first have ended: there workgroups of 512 threads hold up to 96
+// costs in a thread (half as many threads keep half as much beside them), 64 to 8
+// columns, 254 workgroups at 4096.
 //
 // What bounds it: the way of a value from one workgroup to another and the
-// reduction, 1.6 us a layer at 1024 values, 2.6 at 3071 and 4.4 at 4096 (more
-// workgroups than places: two rounds).  A solve of 4096 values and 64 layers takes
-// 275 us where the column-block sweep takes 810, one of 1024 and 16 layers 25
-// where it takes 86.
+// reduction, 1.6 us a layer at 1024 values, 2.6 at 3071 and about 4 at 4096.  A
+// solve of 4096 values and 64 layers takes about 240 us (275 with the workgroups of
+// 1024 threads, in two rounds) where the column-block sweep takes 810, one of 1024
+// and 16 layers 25 where it takes 86.
 #include "device.hpp"
 #include "launch.hpp"
 
@@ -35,11 +38,12 @@ namespace ecasq {
 namespace {
 
 constexpr int kHT = 1024;
-constexpr int kHWaves = kHT / 64;
+constexpr int kHTBig = 512;
 constexpr uint64_t kUnset = ~0ull;
 // polls before a wait gives up (about a second)
 constexpr uint32_t kHeldSpin = 1u << 20;
 constexpr int64_t kNarrowP = 2048;
+constexpr int64_t kBigP = 3072;
 
 struct HeldArgs {
     Hist H;
@@ -86,7 +90,8 @@ __global__ __launch_bounds__(256) void k_held_base(HeldArgs a) {
 
 struct HeldSmem {
     double2 tab[kLog2Size];
-    double part[2][4 * kHWaves * 32];  // each row of 16 lanes' minima of W columns (layer parity)
+    // each row of 16 lanes' minima of W columns (layer parity)
+    double part[2][2048];
     int32_t ticket;
 };
 
@@ -99,7 +104,7 @@ __device__ __forceinline__ double lane_move(double x) {
 constexpr int kXor1 = 0xB1, kXor2 = 0x4E, kXor8 = 0x128;  // quad permutations, row rotation by 8
 
 // F_{i-1} of the thread's predecessors, +inf for those at or past kend.
-template <int R>
+template <int T, int R>
 __device__ __forceinline__ void await(const HeldArgs& a, const double* Fp, int64_t kend,
                                       double (&f)[R]) {
     uint64_t b[R];
@@ -107,7 +112,7 @@ __device__ __forceinline__ void await(const HeldArgs& a, const double* Fp, int64
         bool miss = false;
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            const int64_t k = (int64_t)threadIdx.x + kHT * r;
+            const int64_t k = (int64_t)threadIdx.x + T * r;
             b[r] = 0x7FF0000000000000ull;
             if (k < kend)
                 b[r] = __hip_atomic_load(reinterpret_cast<const uint64_t*>(Fp + k),
@@ -133,9 +138,11 @@ __device__ __forceinline__ void await(const HeldArgs& a, const double* Fp, int64
     for (int r = 0; r < R; r++) f[r] = __longlong_as_double((long long)b[r]);
 }
 
-// Layers 3..I of columns c0 .. c0 + W - 1 (c0 + W <= 1024 R).
-template <int W, int R>
+// Layers 3..I of columns c0 .. c0 + W - 1 (c0 + W - 1 <= T R).
+template <int T, int W, int R>
 __device__ __forceinline__ void held(const HeldArgs& a, int64_t c0, HeldSmem& sm) {
+    constexpr int ROWS = T / 16;  // rows of 16 lanes
+    static_assert(ROWS * W <= 2048 && W / 8 <= T / 64, "a workgroup's minima and their waves");
     const int tid = threadIdx.x, lane = tid % 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int64_t p = a.H.p;
@@ -145,7 +152,7 @@ __device__ __forceinline__ void held(const HeldArgs& a, int64_t c0, HeldSmem& sm
         double v[R], N[R], S[R], S2[R];
 #pragma unroll
         for (int r = 0; r < R; r++) {
-            const int64_t k = min((int64_t)tid + kHT * r, p - 1);
+            const int64_t k = min((int64_t)tid + T * r, p - 1);
             v[r] = a.H.v[k];
             N[r] = a.H.N[k];
             S[r] = a.H.S[k];
@@ -166,7 +173,7 @@ __device__ __forceinline__ void held(const HeldArgs& a, int64_t c0, HeldSmem& sm
                                sm.tab, C, P);
                     e = __builtin_fma(-a.lamp, P, C);
                 }
-                q[r][c] = (int64_t)tid + kHT * r < j && j < p ? e : inf;
+                q[r][c] = (int64_t)tid + T * r < j && j < p ? e : inf;
             }
         }
     }
@@ -174,7 +181,7 @@ __device__ __forceinline__ void held(const HeldArgs& a, int64_t c0, HeldSmem& sm
     for (int32_t i = 3; i <= a.I; i++) {
         double* part = sm.part[i & 1];
         double f[R];
-        await<R>(a, a.F + (int64_t)(i - 1) * a.ld, kend, f);
+        await<T, R>(a, a.F + (int64_t)(i - 1) * a.ld, kend, f);
 #pragma unroll
         for (int g = 0; g < W / 8; g++) {
             double m[8];
@@ -207,7 +214,7 @@ __device__ __forceinline__ void held(const HeldArgs& a, int64_t c0, HeldSmem& sm
             const int col = 8 * wave + lane % 8;
             double z = part[(lane / 8) * W + col];
 #pragma unroll
-            for (int u = 1; u < 8; u++) z = __builtin_fmin(z, part[(8 * u + lane / 8) * W + col]);
+            for (int u = 1; u < ROWS / 8; u++) z = __builtin_fmin(z, part[(8 * u + lane / 8) * W + col]);
             z = __builtin_fmin(z, lane_move<kXor8>(z));
             z = __builtin_fmin(z, __shfl_xor(z, 16));
             z = __builtin_fmin(z, __shfl_xor(z, 32));
@@ -220,27 +227,50 @@ __device__ __forceinline__ void held(const HeldArgs& a, int64_t c0, HeldSmem& sm
     }
 }
 
-__global__ __launch_bounds__(kHT) void k_held(HeldArgs a) {
-    __shared__ HeldSmem sm;
-    if (!live(a)) return;  // uniform
+// The workgroup's place in the order of starting; also loads the log2 table.
+__device__ __forceinline__ int64_t take_ticket(const HeldArgs& a, HeldSmem& sm) {
     if (threadIdx.x == 0)
         sm.ticket = __hip_atomic_fetch_add(a.K + a.nblk + 1, 1, __ATOMIC_RELAXED,
                                            __HIP_MEMORY_SCOPE_AGENT);
     if (a.lamp != 0.0) load_log2_table(sm.tab);
     __syncthreads();
-    const int64_t g = __builtin_amdgcn_readfirstlane(sm.ticket);
+    return __builtin_amdgcn_readfirstlane(sm.ticket);
+}
+
+__global__ __launch_bounds__(kHT) void k_held(HeldArgs a) {
+    __shared__ HeldSmem sm;
+    if (!live(a)) return;  // uniform
+    const int64_t g = take_ticket(a, sm);
     if (a.H.p <= kNarrowP) {
         if (8 * g + 8 <= kHT)
-            held<8, 1>(a, 8 * g, sm);
+            held<kHT, 8, 1>(a, 8 * g, sm);
         else
-            held<8, 2>(a, 8 * g, sm);
+            held<kHT, 8, 2>(a, 8 * g, sm);
     } else if (g < 32) {
-        held<32, 1>(a, 32 * g, sm);
+        held<kHT, 32, 1>(a, 32 * g, sm);
     } else if (g < 96) {
-        held<16, 2>(a, kHT + 16 * (g - 32), sm);
+        held<kHT, 16, 2>(a, kHT + 16 * (g - 32), sm);
     } else {
-        held<8, 4>(a, 2 * kHT + 8 * (g - 96), sm);
+        held<kHT, 8, 3>(a, 2 * kHT + 8 * (g - 96), sm);
     }
+}
+
+// p > kBigP: 8 workgroups of 64 columns, 10 of 48 (512 to 991), 44 of 24 (to 2047), 64 of 16
+// (to 3071), then 8 columns each.
+__global__ __launch_bounds__(kHTBig) void k_held_big(HeldArgs a) {
+    __shared__ HeldSmem sm;
+    if (!live(a)) return;  // uniform
+    const int64_t g = take_ticket(a, sm);
+    if (g < 8)
+        held<kHTBig, 64, 1>(a, 64 * g, sm);
+    else if (g < 18)
+        held<kHTBig, 48, 2>(a, 512 + 48 * (g - 8), sm);
+    else if (g < 62)
+        held<kHTBig, 24, 4>(a, 992 + 24 * (g - 18), sm);
+    else if (g < 126)
+        held<kHTBig, 16, 6>(a, 2048 + 16 * (g - 62), sm);
+    else
+        held<kHTBig, 8, 8>(a, 3072 + 8 * (g - 126), sm);
 }
 
 }  // namespace
@@ -259,8 +289,12 @@ hipError_t launch_held(const SweepSolve& S, hipStream_t st) {
     const int64_t p = S.H.p;
     if (p < 2 || p > kHeldMaxP || a.I < 2) return hipErrorInvalidValue;
     k_held_base<<<dim3((unsigned)((p + 255) / 256), (unsigned)(a.I - 1)), 256, 0, st>>>(a);
-    const int64_t wg = p <= kNarrowP ? (p + 7) / 8 : 96 + (p - kNarrowP + 7) / 8;
-    if (a.I > 2) k_held<<<(unsigned)wg, kHT, 0, st>>>(a);
+    if (a.I > 2 && p > kBigP)
+        k_held_big<<<(unsigned)(126 + (p - kBigP + 7) / 8), kHTBig, 0, st>>>(a);
+    else if (a.I > 2 && p > kNarrowP)
+        k_held<<<(unsigned)(96 + (p - kNarrowP + 7) / 8), kHT, 0, st>>>(a);
+    else if (a.I > 2)
+        k_held<<<(unsigned)((p + 7) / 8), kHT, 0, st>>>(a);
     return hipGetLastError();
 }
 

@@ -19,7 +19,8 @@ def _distinct(x, n):
 
 
 CASES = [(257, 3), (264, 40), (1000, 16), (1024, 5), (1025, 64), (1032, 8), (2048, 33), (2049, 12),
-         (3071, 64), (4095, 6), (4096, 64)]
+         (3071, 64), (3072, 9), (3073, 12),
+         (4095, 6), (4096, 64)]
 
 
 @pytest.mark.parametrize("p,s", CASES)
