@@ -64,52 +64,49 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_hist(const uint32_t* __res
     if (tid < 256) hist[(int64_t)tid * nblk + blockIdx.x] = cnt[tid];
 }
 
-// Exclusive scan of m uint32 values in place, one block of 1024 threads, in
-// tiles of 8192 values staged through LDS (coalesced loads and stores):
-// each thread scans 8 consecutive values of the tile, the thread totals are
-// scanned by wavefront shuffles and then across the 16 wavefronts, and a
-// carry takes each tile's total to the next.
-__global__ __launch_bounds__(1024) void k_scan_u32(uint32_t* __restrict__ a, int64_t m) {
-    constexpr int V = 8, T = 1024 * V;
-    __shared__ uint32_t buf[T];
-    __shared__ uint32_t part[16];
-    const int tid = threadIdx.x;
-    const int lane = tid & 63, wave = tid >> 6;
+// Exclusive scan of each digit's counts over the blocks in place, a workgroup per
+// digit, and the digit's total (one workgroup over all 256 nblk counts took 28 us a
+// pass at 2^20 entries).
+constexpr int kDigT = 256;
+
+__global__ __launch_bounds__(kDigT) void k_scan_digits(uint32_t* __restrict__ hist, int nblk,
+                                                       uint32_t* __restrict__ tot) {
+    constexpr int V = 4, W = kDigT / 64;
+    __shared__ uint32_t part[2][W];
+    const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+    uint32_t* a = hist + (int64_t)blockIdx.x * nblk;
     uint32_t carry = 0;
-    for (int64_t base = 0; base < m; base += T) {
-        const int n = m - base < T ? (int)(m - base) : T;
-        for (int i = tid; i < T; i += 1024) buf[i] = i < n ? a[base + i] : 0u;
-        __syncthreads();
+    int odd = 0;
+    for (int b0 = 0; b0 < nblk; b0 += kDigT * V, odd ^= 1) {
         uint32_t v[V], s = 0;
 #pragma unroll
         for (int u = 0; u < V; u++) {
-            v[u] = buf[tid * V + u];
+            const int i = b0 + tid * V + u;
+            v[u] = i < nblk ? a[i] : 0u;
             s += v[u];
         }
-        // every lane takes part in every shuffle
         uint32_t x = s;
+#pragma unroll
         for (int off = 1; off < 64; off <<= 1) {
             const uint32_t y = __shfl_up(x, off);
             if (lane >= off) x += y;
         }
-        if (lane == 63) part[wave] = x;
+        if (lane == 63) part[odd][wave] = x;
         __syncthreads();
-        uint32_t wpre = 0, total = 0;
-        for (int w = 0; w < 16; w++) {
-            wpre += w < wave ? part[w] : 0u;
-            total += part[w];
+        uint32_t run = carry + x - s;
+#pragma unroll
+        for (int w = 0; w < W; w++) {
+            run += w < wave ? part[odd][w] : 0u;
+            carry += part[odd][w];
         }
-        uint32_t run = carry + wpre + x - s;  // exclusive
 #pragma unroll
         for (int u = 0; u < V; u++) {
-            buf[tid * V + u] = run;
+            const int i = b0 + tid * V + u;
+            if (i < nblk) a[i] = run;
             run += v[u];
         }
-        __syncthreads();
-        for (int i = tid; i < n; i += 1024) a[base + i] = buf[i];
-        carry += total;
-        __syncthreads();  // buf and part are reused by the next tile
     }
+    if (tid == 0) tot[blockIdx.x] = carry;
 }
 
 // Stable scatter of one 8-bit digit.  Items are taken in index order
@@ -118,15 +115,28 @@ __global__ __launch_bounds__(kSortBlock) void k_radix_scatter(const uint32_t* __
                                                               uint32_t* __restrict__ kout,
                                                               int64_t n, int shift,
                                                               const uint32_t* __restrict__ hist,
+                                                              const uint32_t* __restrict__ tot,
                                                               int nblk) {
-    __shared__ uint32_t base[256];
+    __shared__ uint32_t base[256], dpart[4];
     __shared__ uint32_t wcnt[kSortBlock / 64][256];
     const int tid = threadIdx.x;
     const int lane = tid & 63;
     const int wave = tid >> 6;
+    uint32_t own = 0, incl = 0;  // the digit's total, and the totals up to it
     if (tid < 256) {
-        base[tid] = hist[(int64_t)tid * nblk + blockIdx.x];
+        incl = own = tot[tid];
+#pragma unroll
+        for (int off = 1; off < 64; off <<= 1) {
+            const uint32_t y = __shfl_up(incl, off);
+            if (lane >= off) incl += y;
+        }
+        if (lane == 63) dpart[wave] = incl;
         for (int w = 0; w < kSortBlock / 64; w++) wcnt[w][tid] = 0;
+    }
+    __syncthreads();
+    if (tid < 256) {
+        for (int w = 0; w < wave; w++) incl += dpart[w];
+        base[tid] = hist[(int64_t)tid * nblk + blockIdx.x] + incl - own;
     }
     __syncthreads();
     const uint64_t lt_mask = (lane == 0) ? 0ull : (~0ull >> (64 - lane));
@@ -441,7 +451,7 @@ size_t prep_scratch_bytes(int64_t d) {
     b += align256(sizeof(uint32_t) * 256 * nblk);      // digit histogram
     b += align256(sizeof(uint64_t) * kRec * nchunk);   // chunk records
     b += align256(sizeof(uint64_t) * kRec * ((nchunk + kScanBlock - 1) / kScanBlock));  // runs
-    b += align256(sizeof(uint32_t) * 4);               // flags
+    b += align256(sizeof(uint32_t) * 256);             // digit totals
     return b;
 }
 
@@ -477,6 +487,8 @@ hipError_t launch_prep(const void* x, int dt, int64_t d, void* scratch, hipStrea
     uint64_t* rec = reinterpret_cast<uint64_t*>(w);
     w += align256(sizeof(uint64_t) * kRec * nchunk);
     uint64_t* tot = reinterpret_cast<uint64_t*>(w);
+    w += align256(sizeof(uint64_t) * kRec * ((nchunk + kScanBlock - 1) / kScanBlock));
+    uint32_t* dtot = reinterpret_cast<uint32_t*>(w);
 
     const int ig = (int)((d + 255) / 256 < 65536 ? (d + 255) / 256 : 65536);
     if (dt == 0) k_ingest<0><<<ig, 256, 0, st>>>(x, d, k0, flags_dev);
@@ -487,8 +499,9 @@ hipError_t launch_prep(const void* x, int dt, int64_t d, void* scratch, hipStrea
     // all zeros or, below zero, all ones, so two or three passes sort them.
     for (int shift = dt == 0 ? 0 : dt == 1 ? 13 : 16; shift < 32; shift += 8) {
         k_radix_hist<<<(unsigned)nblk, kSortBlock, 0, st>>>(k0, d, shift, hist, (int)nblk);
-        k_scan_u32<<<1, 1024, 0, st>>>(hist, 256 * nblk);
-        k_radix_scatter<<<(unsigned)nblk, kSortBlock, 0, st>>>(k0, k1, d, shift, hist, (int)nblk);
+        k_scan_digits<<<256, kDigT, 0, st>>>(hist, (int)nblk, dtot);
+        k_radix_scatter<<<(unsigned)nblk, kSortBlock, 0, st>>>(k0, k1, d, shift, hist, dtot,
+                                                               (int)nblk);
         uint32_t* t = k0;
         k0 = k1;
         k1 = t;

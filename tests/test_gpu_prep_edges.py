@@ -44,3 +44,20 @@ def test_prep_reports_nonfinite(d, bad):
     with pytest.raises(ecasq.EcasqError) as e:
         ecasq.ecasq_histogram(x)
     assert e.value.status == ecasq.ECASQ_ENONFINITE
+
+
+def test_prep_more_than_1024_tiles():
+    """More key tiles than one step of a digit's scan takes (1024): the sorted values
+    and counts against torch's sort, the sums within the rounding of a 64-bit sum of
+    n terms of one sign, n 2^-53 of it."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    d = (1 << 22) + 4097
+    print("[case] prep", d, flush=True)
+    x = torch.rand(d, generator=torch.Generator("cuda").manual_seed(5), device="cuda")
+    v, N, S, S2 = ecasq.ecasq_histogram(x)
+    u, c = torch.unique(x, return_counts=True)
+    assert torch.equal(v, u.double())
+    assert torch.equal(N, torch.cumsum(c, 0).double())
+    t = torch.cumsum(u.double() * c, 0)
+    assert bool(((S - t).abs() <= d * 2.0 ** -53 * t + 1e-300).all())
