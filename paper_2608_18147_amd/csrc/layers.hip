@@ -171,28 +171,39 @@ struct Cols {
     double sN;           // sqrt(N S2) at the last column
     double nu, n0, n1;   // N_j - N_first lies in nu (v_j - v_first) + [n0, n1], in entries / d
     double alpha, beta;  // u_j <= alpha + beta (v_j - v_first); alpha = -inf: no column has a chain
-    double aa;           // |alpha|, 0 for -inf
+    double aa;           // the larger |alpha + beta (v_j - v_first)| of the ends, 0 for -inf
     double db;           // v_last - v_first
 };
 
-// A lower bound of the least h over [lo, hi].
-__device__ __forceinline__ float h_floor1(double y) {
-    const float a = (float)y;
-    return a > 1e-30f ? a * (-__builtin_amdgcn_logf(a) * (1.0f - 0x1p-18f) - 0x1p-20f) : 0.0f;
+// A lower bound of h(y) for a computed frequency y, clamped at 0 as the cell clamps it.
+// h is negative above 1: exact frequencies stay below it, but the computed ones pass it
+// where the prefix sums cancel (an entry of 1e16 times the others' spread takes their sums
+// with it, and a grid's steps may lie far below an ulp of its values).
+__device__ __forceinline__ float h_floor1(float y) {
+    const float l = -__builtin_amdgcn_logf(y);
+    return y > 1e-30f
+               ? y * (__builtin_fmaf(-0x1p-18f, __builtin_fabsf(l), l) - 0x1p-20f)
+               : 0.0f;
 }
-__device__ __forceinline__ float h_floor(double lo, double hi) {
-    return __builtin_fmaxf(__builtin_fminf(h_floor1(lo), h_floor1(hi)), 0.0f);
+// The least h over [lo, hi]: h is concave, so it lies at an end.
+__device__ __forceinline__ float h_floor(float lo, float hi) {
+    return __builtin_fminf(h_floor1(lo), h_floor1(hi));
 }
+// A computed frequency passes an exact one (at most 1) by at most e.
+__device__ __forceinline__ float freq_cap(double e) { return (float)(1.0 + 0x1p-20 + e); }
 
 // The same over [lo, hi] whose ends move on straight lines from (lo0, hi0) to
 // (lo1, hi1): h of each end is concave along the way, so the least h lies above
-// the line between the two bounds added to f0 and f1.  That needs the ends in
-// (0, 1]; elsewhere 0 is added.
+// the line between the two bounds added to f0 and f1.  That needs the ends above 0;
+// there, and where an end passes 1 (the cap is the better bound), the least h over
+// all of the range below the cap is added instead.
 __device__ __forceinline__ void h_floor_line(double lo0, double hi0, double lo1, double hi1,
-                                             float& f0, float& f1) {
-    const bool ok = __builtin_fmin(lo0, lo1) > 1e-30 && __builtin_fmax(hi0, hi1) <= 1.0;
-    f0 += ok ? h_floor(lo0, hi0) : 0.0f;
-    f1 += ok ? h_floor(lo1, hi1) : 0.0f;
+                                             float cap, float& f0, float& f1) {
+    const float l0 = (float)lo0, l1 = (float)lo1, h0 = (float)hi0, h1 = (float)hi1;
+    const float hm = __builtin_fmaxf(h0, h1), hc = __builtin_fminf(hm, cap);
+    const bool ok = __builtin_fminf(l0, l1) > 1e-30f && hm <= 1.0f;
+    f0 += h_floor(ok ? l0 : 0.0f, ok ? h0 : hc);
+    f1 += h_floor(ok ? l1 : 0.0f, ok ? h1 : hc);
 }
 
 // False if predecessor (vn, ss) with F_{i-1} = f cannot hold the minimum of any
@@ -221,10 +232,12 @@ __device__ __forceinline__ bool may_hold(double f, double2 vn, double2 ss, const
         const double tu1 = __builtin_fma(-vn.x, c.vn1.y - vn.y, c.ss1.x - ss.x);
         const double rA = tul * r1 * r1 * (rd * (1.0 - 0x1p-18));
         const double rB = (tu1 + eS) * r0 * r0 * (rd * (1.0 + 0x1p-18));
+        const float cap = freq_cap(e);
         float phi0 = 0.0f, phi1 = 0.0f;
         h_floor_line(uA + c.n0, uB + c.n1, __builtin_fma(c.db, c.nu - rB, uA + c.n0),
-                     __builtin_fma(c.db, c.nu - rA, uB + c.n1), phi0, phi1);
-        h_floor_line(dA, dB, __builtin_fma(c.db, rA, dA), __builtin_fma(c.db, rB, dB), phi0, phi1);
+                     __builtin_fma(c.db, c.nu - rA, uB + c.n1), cap, phi0, phi1);
+        h_floor_line(dA, dB, __builtin_fma(c.db, rA, dA), __builtin_fma(c.db, rB, dB), cap, phi0,
+                     phi1);
         base0 = __builtin_fma(lamp, (double)phi0 - 0x1p-40, base0);
         base1 = __builtin_fma(lamp, (double)phi1 - 0x1p-40, base1);
     }
@@ -233,14 +246,15 @@ __device__ __forceinline__ bool may_hold(double f, double2 vn, double2 ss, const
 
 // Four corners of a line's rectangle: as h_floor_line over both directions.
 __device__ __forceinline__ void h_floor_rect(double lo, double hi, double lt, double ht, double lb,
-                                             double hb, float (&f)[4]) {
-    const double l[4] = {lo, lo + lt, lo + lb, lo + lt + lb};
-    const double h[4] = {hi, hi + ht, hi + hb, hi + ht + hb};
-    const bool ok = __builtin_fmin(__builtin_fmin(l[0], l[1]), __builtin_fmin(l[2], l[3])) >
-                        1e-30 &&
-                    __builtin_fmax(__builtin_fmax(h[0], h[1]), __builtin_fmax(h[2], h[3])) <= 1.0;
+                                             double hb, float cap, float (&f)[4]) {
+    const float l[4] = {(float)lo, (float)(lo + lt), (float)(lo + lb), (float)(lo + lt + lb)};
+    const float h[4] = {(float)hi, (float)(hi + ht), (float)(hi + hb), (float)(hi + ht + hb)};
+    const float lm = __builtin_fminf(__builtin_fminf(l[0], l[1]), __builtin_fminf(l[2], l[3]));
+    const float hm = __builtin_fmaxf(__builtin_fmaxf(h[0], h[1]), __builtin_fmaxf(h[2], h[3]));
+    const float hc = __builtin_fminf(hm, cap);
+    const bool ok = lm > 1e-30f && hm <= 1.0f;
 #pragma unroll
-    for (int x = 0; x < 4; x++) f[x] += ok ? h_floor(l[x], h[x]) : 0.0f;
+    for (int x = 0; x < 4; x++) f[x] += h_floor(ok ? l[x] : 0.0f, ok ? h[x] : hc);
 }
 
 // False if no predecessor of a unit (its end values at o, F_{i-1} above the
@@ -279,13 +293,15 @@ __device__ __forceinline__ bool unit_may_hold(const double2* __restrict__ o, dou
         // towards the last column: D rises by tu / (b - a)^2, U by that of N less it
         const double tu1 = __builtin_fma(-vn0.x, c.vn1.y - vn0.y, c.ss1.x - ss0.x) + eS;
         const double rA = c.db * (tul * r1 * r1 * lo), rB = c.db * (tu1 * rS * rS * hi);
+        const float cap = freq_cap(e);
         float phi[4] = {0.0f, 0.0f, 0.0f, 0.0f};
         const double mc = c.db * c.nu, mu = nu * rd;
         h_floor_rect(__builtin_fma(U, 1.0 - 0x1p-20, c.n0 - e),
-                     __builtin_fma(U, 1.0 + 0x1p-20, c.n1 + e), qA, qB, mc - rB, mc - rA, phi);
+                     __builtin_fma(U, 1.0 + 0x1p-20, c.n1 + e), qA, qB, mc - rB, mc - rA, cap,
+                     phi);
         h_floor_rect(__builtin_fma(D, 1.0 - 0x1p-20, __builtin_fma(u01.x, rd, -e)),
                      __builtin_fma(D, 1.0 + 0x1p-20, __builtin_fma(u01.y, rd, e)), mu - qB,
-                     mu - qA, rA, rB, phi);
+                     mu - qA, rA, rB, cap, phi);
 #pragma unroll
         for (int x = 0; x < 4; x++) b[x] = __builtin_fma(lamp, (double)phi[x] - 0x1p-40, b[x]);
     }
@@ -310,11 +326,13 @@ __device__ __forceinline__ bool span_may_hold(double f, double2 vn1, double2 ss1
         const double r1 = __builtin_amdgcn_rcp(c.vn1.x - vn0.x) * rd;
         const double e = eS * rS;
         const double n1 = c.vn1.y - vn0.y, s1 = c.ss1.x - ss0.x;
-        const float phi =
-            h_floor(__builtin_fma(tu0 * r1, 1.0 - 0x1p-20, -e),
-                    __builtin_fma(__builtin_fma(-vn0.x, n1, s1) * rS, 1.0 + 0x1p-20, e)) +
-            h_floor(__builtin_fma(__builtin_fma(c.vn0.x, n0, -sa) * r1, 1.0 - 0x1p-20, -e),
-                    __builtin_fma(__builtin_fma(c.vn1.x, n1, -s1) * rS, 1.0 + 0x1p-20, e));
+        const float cap = freq_cap(e);
+        auto range = [&](double tl, double th) {  // between tl r1 and th rS
+            return h_floor((float)__builtin_fma(tl * r1, 1.0 - 0x1p-20, -e),
+                           __builtin_fminf((float)__builtin_fma(th * rS, 1.0 + 0x1p-20, e), cap));
+        };
+        const float phi = range(tu0, __builtin_fma(-vn0.x, n1, s1)) +
+                          range(__builtin_fma(c.vn0.x, n0, -sa), __builtin_fma(c.vn1.x, n1, -s1));
         base = __builtin_fma(lamp, (double)phi - 0x1p-40, base);
     }
     const double rise = c.db * __builtin_fmax(tu0 - eS, 0.0);
@@ -367,7 +385,10 @@ __device__ __forceinline__ Cols make_cols(const Hist& H, int64_t f0, int64_t l0,
         n1 = __builtin_fmax(n1, __shfl_xor(n1, off));
     }
     r.alpha = uniform(al);
-    r.aa = r.alpha > -__builtin_huge_val() ? __builtin_fabs(r.alpha) : 0.0;
+    r.aa = r.alpha > -__builtin_huge_val()
+               ? __builtin_fmax(__builtin_fabs(r.alpha),
+                                __builtin_fabs(__builtin_fma(r.beta, r.db, r.alpha)))
+               : 0.0;
     r.nu = uniform(r.nu * rd);
     // (rounding of the line: 2^-40 of the largest step)
     r.n0 = uniform((n0 - 0x1p-40 * (r.vn1.y - r.vn0.y)) * rd);

@@ -86,3 +86,68 @@ def test_layers_hold_every_minimum(case):
             np.testing.assert_array_equal(F[i, cols], Fo, err_msg=f"{name} {lam} layer {i}")
             if i < 4:  # columns no chain of i values reaches
                 assert np.all(np.isinf(F[i, : i - 1])) or i == 2
+
+
+def _cancelled(n, centre, spread, big):
+    """Values around centre and one entry that takes their prefix sums with it."""
+    x = (centre + spread * np.random.default_rng(13).standard_normal(n)).astype(np.float32)
+    x[7] = big
+    return x
+
+
+@pytest.mark.parametrize("big", [-1e16, -1e18, 1e20, -1e20, -1e30])
+@pytest.mark.parametrize("centre,spread", [(1.0, 0.1), (10.0, 1.0), (1000.0, 1.0)])
+@pytest.mark.parametrize("n,s", [(6000, 8), (53000, 5)])
+def test_layers_where_sums_cancel(n, s, centre, spread, big):
+    """Sums rounded to 53 bits leave frequencies far outside [0, 1] here, and entropy terms
+    far below 0: every column of every layer against the layer-by-layer schedule, which
+    evaluates every predecessor, and the codebooks of the two."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x = _cancelled(n, centre, spread, big)
+    xd = torch.from_numpy(x).to("cuda")
+    p = np.unique(x).size
+    assert p > 4096 and p > 64 * s
+    opts = [ecasq.ecasq_default_options(dp_schedule=1, refine_rounds=0),
+            ecasq.ecasq_default_options(dp_schedule=0, recovery=1, refine_rounds=0)]
+    for lam in (0.0, 0.003, 0.2, 50.0):
+        print("[case] cancelled", n, s, centre, spread, big, lam, flush=True)
+        F1, _, _, _, r1 = ecasq.ecasq_dp_trace(xd, s, lam, schedule=1, argmins=False)
+        F0, _, _, _, r0 = ecasq.ecasq_dp_trace(xd, s, lam, schedule=0)
+        for i in range(2, s + 1):
+            bad = int((F1[i, i - 1:p] != F0[i, i - 1:p]).sum())
+            assert bad == 0, f"lambda {lam} layer {i}: {bad} columns"
+        assert r1[0] == r0[0] and r1[3] == r0[3]
+        (c1, k1, i1), (c0, k0, i0) = (ecasq.ecasq_solve_lagrangian(xd, s, lam, options=o)
+                                      for o in opts)
+        assert torch.equal(k1, k0) and torch.equal(c1, c0) and i1["mse"] == i0["mse"]
+
+
+@pytest.mark.parametrize("kind", ["narrow", "narrow_rare", "offset", "outlier"])
+@pytest.mark.parametrize("m,s", [(5000, 6), (8000, 9)])
+def test_layers_on_a_uniform_grid(m, s, kind):
+    """A grid's points are 53-bit values: on a narrow range far from zero its steps lie far
+    below an ulp of the entries.  The codebooks of the two schedules."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    rng = np.random.default_rng(m)
+    n = 20000
+    if kind == "narrow":
+        x = 1.0 + 2.0 ** -23 * rng.integers(0, 3, n)
+    elif kind == "narrow_rare":
+        x = np.full(n, 1.0 + 2.0 ** -23)
+        x[:5] = 1.0
+    elif kind == "offset":
+        x = 1000.0 + rng.standard_normal(n)
+    else:
+        x = 5.0 + rng.standard_normal(n)
+        x[3] = -1e20
+    xd = torch.from_numpy(x.astype(np.float32)).to("cuda")
+    for lam in (0.0, 0.01, 1.0):
+        print("[case] grid", kind, m, s, lam, flush=True)
+        (c1, k1, i1), (c0, k0, i0) = (
+            ecasq.ecasq_solve_lagrangian(xd, s, lam, options=ecasq.ecasq_default_options(
+                alphabet=1, alphabet_size=m, refine_rounds=0, **kw))
+            for kw in (dict(dp_schedule=1), dict(dp_schedule=0, recovery=1)))
+        assert i1["p"] > 4096 and i1["p"] > 64 * s, "sizes that take the layers with bounds"
+        assert torch.equal(k1, k0) and torch.equal(c1, c0) and i1["mse"] == i0["mse"]
