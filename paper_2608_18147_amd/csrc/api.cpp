@@ -257,7 +257,8 @@ struct Ctx {
     int64_t cells;
     int32_t solves;
     bool own;
-    bool sweep;  // dp_APX by the column-block sweep (else layer by layer)
+    bool sweep;  // schedule 1 (else layer by layer)
+    bool bounds = true;  // no solve by the layers with bounds has given up
     // search points: 0 dp_APX (H(I,B)), 1 the optimal DP (H(Xhat)), 2 dp_APX's
     // codebook refined at the query's multiplier (H(Xhat))
     int32_t objective = 0;
@@ -396,14 +397,17 @@ SweepSolve sweep_args(const Ctx& c) {
     S.ld = c.d;
     S.I = (int32_t)std::min<int64_t>(c.s, c.p);
     S.lamp = 0.0;
+    S.bounds = c.bounds;
     return S;
 }
 
 // Enqueue one dp_APX solve by the sweep whose lambda' and run flag the
 // kernels read from device memory (the device-resident search); the result
 // (J, MSE, H(I,B), t) goes to the res slot and the codebook to the chain slot.
-ecasq_status sweep_enqueue(Ctx& c, const double* lampp, const int32_t* runp, int32_t exact_s) {
+ecasq_status sweep_enqueue(Ctx& c, const double* lampp, const int32_t* runp, int32_t exact_s,
+                           bool bounds) {
     SweepSolve S = sweep_args(c);
+    S.bounds = bounds;
     S.lampp = lampp;
     S.runp = runp;
     timing_begin(2, dp_cells(c.p, S.I), c.st);
@@ -422,9 +426,20 @@ ecasq_status sweep_solve(Ctx& c, double lam, int32_t exact_s, Point& out, double
     S.lamp = lam * c.s2tot;
     double* res = c.at<double>(c.L.res);
     int32_t* ch = c.at<int32_t>(c.L.swchain);
-    timing_begin(2, dp_cells(p, imax), c.st);
-    HIP_TRY(launch_sweep(S, exact_s, res, ch, c.st));
-    timing_end(c.st);
+    double* r = c.host.at<double>(HostBlock::kSmall);
+    int32_t* hc = c.host.at<int32_t>(HostBlock::kChains);
+    for (;;) {
+        timing_begin(2, dp_cells(p, imax), c.st);
+        HIP_TRY(launch_sweep(S, exact_s, res, ch, c.st));
+        timing_end(c.st);
+        HIP_TRY(hipMemcpyAsync(r, res, sizeof(double) * 4, hipMemcpyDeviceToHost, c.st));
+        HIP_TRY(hipMemcpyAsync(hc, ch, sizeof(int32_t) * imax, hipMemcpyDeviceToHost, c.st));
+        HIP_TRY(hipStreamSynchronize(c.st));
+        if (r[3] != -(double)kSweepGaveUp || !S.bounds) break;
+        S.bounds = false;
+        if (lam != 0.0) c.bounds = false;
+    }
+    timing_flush();
     if (dump) {
         const int32_t ls = c.s + 1;
         const int64_t ds = dump->stride;
@@ -441,13 +456,7 @@ ecasq_status sweep_solve(Ctx& c, double lam, int32_t exact_s, Point& out, double
             HIP_TRY(launch_sweep_accumulators(S, dump->M + (int64_t)m * ls * ds,
                                               dump->P + (int64_t)m * ls * ds, c.st));
     }
-    double* r = c.host.at<double>(HostBlock::kSmall);
-    const int32_t* hc = c.host.at<int32_t>(HostBlock::kChains);
-    HIP_TRY(hipMemcpyAsync(r, res, sizeof(double) * 4, hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipMemcpyAsync(c.host.at<int32_t>(HostBlock::kChains), ch, sizeof(int32_t) * imax,
-                           hipMemcpyDeviceToHost, c.st));
-    HIP_TRY(hipStreamSynchronize(c.st));
-    timing_flush();
+    if (dump) HIP_TRY(hipStreamSynchronize(c.st));
     const int32_t t = (int32_t)r[3];
     if (t < 2 || t > imax) return ECASQ_EHIP;
     out.chain.assign(hc, hc + t);
@@ -768,11 +777,14 @@ ecasq_status search_device_loop(Ctx& c, int32_t exact_s, int32_t max_passes, boo
         HIP_TRY(hipStreamSynchronize(c.st));
         if (poll[0].done) return ECASQ_OK;
     }
-    const int32_t limit = 2 * max_passes + 8;  // each solve adds a point to a finite search
+    // each solve adds a point to a finite search, but two at lambda = 0 and two later that
+    // may give up
+    const int32_t limit = 2 * max_passes + 12;
+    bool bounds = c.bounds;
     const int32_t ahead = (c.p + 63) / 64 < kAheadBlocks ? 1 : 0;
     int32_t n = 0;
     for (;;) {
-        ECASQ_TRY(sweep_enqueue(c, &S->todo_lamp[0], &S->run, exact_s));
+        ECASQ_TRY(sweep_enqueue(c, &S->todo_lamp[0], &S->run, exact_s, bounds));
         HIP_TRY(launch_search_commit(S, res, ch, 1, pch, 1, poll + (n & 1), c.st));
         HIP_TRY(hipEventRecord(c.host.ev[n & 1], c.st));
         n++;
@@ -781,7 +793,9 @@ ecasq_status search_device_loop(Ctx& c, int32_t exact_s, int32_t max_passes, boo
             const int32_t k = (n - 1 - ahead) & 1;
             HIP_TRY(hipEventSynchronize(c.host.ev[k]));
             const SearchPeek& pk = poll[k];
-            if (timing_verbose()) print_point(pk.nsol, pk.last);
+            if (pk.gave_up == 2) c.bounds = false;
+            bounds = c.bounds && !pk.gave_up;
+            if (timing_verbose() && !pk.gave_up) print_point(pk.nsol, pk.last);
             if (pk.done) break;  // a queued solve finds run = 0
         }
         if (n > limit) return ECASQ_EHIP;

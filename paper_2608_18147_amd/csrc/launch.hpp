@@ -158,7 +158,12 @@ struct SweepSolve {
     double lamp;   // lambda' in MSE units (when lampp is null)
     const double* lampp = nullptr;  // device: lambda', read by the kernels
     const int32_t* runp = nullptr;  // device: 0 = skip the whole solve (null: run)
+    bool bounds = true;  // the layers with bounds may be taken (false: after one gave up)
 };
+// A solve by the layers with bounds that would take longer than the sweep gives up: in
+// its failure word, and as -kSweepGaveUp in place of the number of values (out[3]; 0 there
+// is a failed solve).
+constexpr int32_t kSweepGaveUp = 2;
 size_t sweep_table_bytes(int64_t d, int32_t s);
 // Bytes of K that a solve needs for p <= d: the steps' counters and the
 // traceback's partials (the argmin table is (s + 1) d int32 on top).
@@ -196,7 +201,9 @@ struct SearchPt {
     int32_t t, pad;
 };
 struct SearchPeek {
-    int32_t done, nsol;
+    int16_t done;
+    int16_t gave_up;  // the solve before gave up: 1 at lambda = 0, 2 elsewhere (else 0)
+    int32_t nsol;
     SearchPt last;
 };
 struct SearchState {
@@ -225,7 +232,8 @@ hipError_t launch_search_begin(SearchState* S, const SearchParams& P, const doub
 // (device) holds 4 doubles per point (J, MSE, H, t); chains (device, stride
 // S->s, may be null) their codebooks, copied into pchains (kSearchMaxPts x s)
 // when S->has_chain.  With gate != 0 the kernel does nothing unless S->run is
-// set (a solve that was skipped because the search had ended).  peek_out (pinned
+// set (a solve that was skipped because the search had ended).  A solve that gave up
+// (m = 1) adds no point: the search waits for the next commit.  peek_out (pinned
 // host memory, may be null) receives S->peek.
 hipError_t launch_search_commit(SearchState* S, const double* res, const int32_t* chains,
                                 int32_t m, int32_t* pchains, int32_t gate, SearchPeek* peek_out,

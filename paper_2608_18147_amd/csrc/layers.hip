@@ -65,6 +65,36 @@ constexpr int kGC = 16;       // columns of a wavefront (4 predecessors side by 
 constexpr int64_t kWideP = 49152;
 constexpr int kList = 1024;   // blocks tested per round (those left are listed in LDS)
 
+// What is left of the far predecessors after the tests of units, in steps of a wavefront: one
+// for four predecessors evaluated, four for 64 tested one by one.  Few for ordinary inputs; most
+// of the predecessors where prefix sums cancel so far that no bound holds (values over 60
+// decades, an outlier of 1e18), and then the sweep, which forms each cost once for all
+// layers, is up to ten times faster (2^18 such values, 32 layers: 1390 ms against 132).  So the
+// steps are counted: a workgroup reports its own, between rounds and at its end, once a
+// wavefront has p / 32 of them in a layer (fewer for many layers; most never do), and adds them to
+// a word only where needed, since additions to one word wait for each other, 6 ns each.  When the
+// longest chains of the layers and a kCrowd-th of all steps pass the layer's limit, the
+// solve gives up (the failure word is kSweepGaveUp) and the host takes the sweep: 161 ms in
+// that example, 3.4 against 2.9 for 16384 values.  Counting costs ordinary inputs 0 to 2.5%.
+struct LayWork {
+    unsigned long long all;
+    uint32_t chain;       // sum over the layers of the most steps of a wavefront
+    uint32_t longest[2];  // that of the layer (parity)
+    uint32_t gone[2];     // the layer or one before it has given up (parity)
+    uint32_t pad;
+    int32_t* fail;        // the failure word
+    uint32_t limit[256];  // of each layer
+};
+constexpr uint32_t kCrowd = 2048;
+constexpr size_t kWorkBytes = 2048;
+static_assert(sizeof(LayWork) <= kWorkBytes, "the work words fit before the units");
+constexpr uint32_t kSample = 16;  // one workgroup of so many adds to `all`
+
+template <class T>
+__device__ __forceinline__ T fresh(const T* at) {
+    return __hip_atomic_load(at, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+}
+
 struct LayArgs {
     Hist H;
     double* F;    // [I+1][ld], rows 2..I
@@ -72,7 +102,7 @@ struct LayArgs {
                   // first, and how far N_last - N_k lies from its line
     double2* LN;  // two rows of nun: F_i[k] >= x + y (v_k - v_first) in the unit (layer parity)
     double* FE;   // two rows of nun: F_i at the unit's last value
-    int32_t* K;   // K[nblk]: the failure word of eq. apx_final's kernel (cleared)
+    int32_t* K;   // K[nblk]: the failure word of eq. apx_final's kernel
     int64_t ld, nblk, nun;
     int32_t I;
     double lamp;
@@ -87,6 +117,26 @@ __device__ __forceinline__ bool live(LayArgs& a) {
     if (a.runp && *a.runp == 0) return false;
     if (a.lampp) a.lamp = *a.lampp;
     return true;
+}
+
+// The steps up to layer i at whose rate the layers after it would take as long as the whole
+// solve by the sweep, and a twentieth of the sweep's time on top for layers that need more than
+// the rest.  In microseconds: the sweep's time (a chain of blocks for few values, cells at a
+// rate for many: 5000 values and 16 layers 0.58 ms, 16384 and 32 2.6, 128 5.6, 65536 and 32
+// 13.2, 2^18 and 32 132 and 95 at lambda = 0), a layer with few steps, and 0.18 for a step (0.166 to 0.184 from
+// inputs with 1000 to 5000 steps of a wavefront in a layer; half at lambda = 0).
+__device__ __forceinline__ uint32_t work_limit(int64_t p, int32_t I, int32_t i, bool zero) {
+    const double n = (double)p, left = (double)(I - i);
+    if (left < 1.0) return 0xFFFFFFFFu;
+    const double sweep =
+        n * __builtin_fmax(0.08 + 0.002 * I + 7e-7 * n, (zero ? 4.4e-8 : 6.2e-8) * n * I);
+    const double layer = 18.0 + n / 1500.0;
+    const double us = 0.05 * sweep + (double)(i - 2) * __builtin_fmax(0.0, sweep / left - layer);
+    return (uint32_t)__builtin_fmin(us / (zero ? 0.09 : 0.18), 4e9);
+}
+
+__device__ __forceinline__ LayWork* work_of(const LayArgs& a) {
+    return reinterpret_cast<LayWork*>(reinterpret_cast<char*>(a.SB) - kWorkBytes);
 }
 
 // A line under F_i over each unit of UN columns and F_i at its end, as the next
@@ -161,7 +211,17 @@ __global__ __launch_bounds__(256) void k_layer_base(LayArgs a) {
         }
     }
     put_summary<UN>(a, 2, j, f, vn.x);
-    if (j == 0) a.K[a.nblk] = 0;
+    if (blockIdx.x == 0) {  // (256 threads, and at most 255 layers)
+        LayWork* W = work_of(a);
+        if (threadIdx.x == 0) {
+            a.K[a.nblk] = 0;
+            W->all = 0;
+            W->chain = 0;
+            W->longest[0] = W->longest[1] = W->gone[0] = W->gone[1] = 0;
+            W->fail = a.K + a.nblk;
+        }
+        W->limit[threadIdx.x] = work_limit(p, a.I, (int32_t)threadIdx.x, a.lamp == 0.0);
+    }
 }
 
 // What the tests know of a set of columns.
@@ -414,7 +474,18 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
     __shared__ uint16_t slist[SUP ? kList : 1];
     __shared__ uint16_t list[kList], glist[CW > 1 ? CW : 1][kList], clist[CW][kList];
     __shared__ int32_t nslist, nlist, nglist[CW], nclist[CW];
-    if (!live(a)) return;  // uniform
+    __shared__ uint32_t steps[W], told, stop;
+    {
+        // three loads in flight together (gone: written by earlier launches only)
+        const int32_t run = a.runp ? *a.runp : 1;
+        LayWork* work = work_of(a);
+        const uint32_t gone = work->gone[(i - 1) & 1];
+        if (a.lampp) a.lamp = *a.lampp;
+        if (run == 0 || gone != 0) {  // uniform
+            if (gone != 0 && blockIdx.x == 0 && threadIdx.x == 0) work->gone[i & 1] = 1;
+            return;
+        }
+    }
     const int tid = threadIdx.x, lane = tid % 64;
     const int wave = __builtin_amdgcn_readfirstlane(tid / 64);
     const int cg = wave % CW, sl = wave / CW;
@@ -455,6 +526,12 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
 #pragma unroll
         for (int s = 0; s < KS; s++) best = __builtin_fmin(best, red[s][kGC * cg + c]);
     };
+    if (tid == 0) {
+        stop = told = 0;
+#pragma unroll
+        for (int w = 0; w < W; w++) steps[w] = 0;
+        if (blockIdx.x == 0) work_of(a)->longest[(i + 1) & 1] = 0;
+    }
     __syncthreads();  // the table
     // the far units that are best for columns j0 and j1, judged by their last
     // predecessors; the end of each is the middle of 128 predecessors, from kA and
@@ -565,6 +642,31 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
         }
         return __builtin_popcountll(mask);
     };
+    // Thread 0: the workgroup's steps so far (see LayWork).
+    LayWork* work = work_of(a);
+    auto report = [&]() {
+        uint32_t most = 0, sum = 0;
+#pragma unroll
+        for (int w = 0; w < W; w++) {
+            most = max(most, steps[w]);
+            sum += steps[w];
+        }
+        if ((int64_t)most < p >> (a.I < 64 ? 5 : a.I < 128 ? 6 : 7)) return;
+        uint32_t had = fresh(&work->longest[i & 1]);
+        if (most > had) {
+            had = atomicMax(&work->longest[i & 1], most);
+            if (most > had) atomicAdd(&work->chain, most - had);
+        }
+        if (blockIdx.x % kSample == 0) {
+            atomicAdd(&work->all, (unsigned long long)kSample * (sum - told));
+            told = sum;
+        }
+        if (fresh(&work->chain) + fresh(&work->all) / kCrowd > work->limit[i]) {
+            *work->fail = kSweepGaveUp;
+            __hip_atomic_store(&work->gone[i & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+        }
+        stop = fresh(&work->gone[i & 1]);
+    };
     auto run = [&](int ns) {
         if (ns == 0) return;
         __builtin_amdgcn_fence(__ATOMIC_ACQ_REL, "wavefront");
@@ -617,9 +719,14 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
         // one round: at most kList units, unit(x) for x < nx
         auto round = [&](int nx, auto unit) {
             __syncthreads();  // the lists are free
-            if (tid == 0) nlist = 0;
+            if (tid == 0) {
+                nlist = 0;
+                report();
+            }
             if (tid < CW) nglist[tid] = nclist[tid] = 0;
             __syncthreads();
+            if (stop) return;  // uniform
+            uint32_t done = 0;
             for (int x = tid; x < nx; x += T) {
                 const int64_t q = unit(x), dA = q * UN - kA, dB = q * UN - kB;
                 if (q < qn && (dA < 0 || dA >= 2 * kSB) && (dB < 0 || dB >= 2 * kSB) &&
@@ -646,6 +753,7 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
             if (nl > kMany) {  // uniform in the workgroup
                 // many are left: each unit against each column, 4 units at a time
                 for (int x = 4 * sl; x < n; x += 4 * KS) {
+                    done += 4;
                     bool any = false;
                     int o = 0;
                     if (x + kq < n) {
@@ -674,7 +782,9 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
                 // the next loads are in flight while these are evaluated
                 if (x + KS < nw) next(x + KS);
                 run(ns);
+                done += 4 + (uint32_t)(ns + 3) / 4;
             }
+            if (lane == 0) steps[wave] += done;
         };
         if constexpr (SUP) {
             const int64_t nsup = (qn + 7) / 8;
@@ -719,6 +829,7 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
             a.F[(int64_t)i * a.ld + jo] = fo;
         }
         if (tid < NC) put_summary<UN>(a, i, jo, fo, a.H.v[min(jo, p - 1)]);
+        if (tid == 0 && qn > 0) report();
     }
 }
 
@@ -734,11 +845,12 @@ hipError_t launch_all(LayArgs a, hipStream_t st) {
 
 }  // namespace
 
-// The units' end values, then the two rows of lines and of unit-end values (a
+// The work words, the units' end values, then the two rows of lines and of unit-end values (a
 // unit is at least 16 values).
 size_t layers_scratch_bytes(int64_t d) {
     const size_t nun = (size_t)(d + kGC - 1) / kGC;
-    return align256(16 * kUnit * nun) + align256(2 * 16 * nun) + align256(2 * 8 * nun);
+    return kWorkBytes + align256(16 * kUnit * nun) + align256(2 * 16 * nun) +
+           align256(2 * 8 * nun);
 }
 
 hipError_t launch_layers(const SweepSolve& S, hipStream_t st) {
@@ -747,7 +859,7 @@ hipError_t launch_layers(const SweepSolve& S, hipStream_t st) {
     a.F = S.F;
     a.nblk = (S.H.p + kSB - 1) / kSB;
     a.nun = (S.H.p + kGC - 1) / kGC;
-    char* o = S.B;
+    char* o = S.B + kWorkBytes;
     a.SB = reinterpret_cast<double2*>(o);
     o += align256(16 * kUnit * (size_t)a.nun);
     a.LN = reinterpret_cast<double2*>(o);

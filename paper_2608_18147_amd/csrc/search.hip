@@ -42,7 +42,7 @@ __device__ int find_point(const SearchState& S, double lam) {
 
 // What the host polls between solves: done, solves so far, the last point.
 __device__ void peek(SearchState& S) {
-    S.peek.done = S.done;
+    S.peek.done = (int16_t)S.done;
     S.peek.nsol = S.nsol;
     if (S.npts > 0) S.peek.last = S.pts[S.npts - 1];
 }
@@ -238,6 +238,7 @@ __global__ __launch_bounds__(64) void k_search_begin(SearchState* __restrict__ S
     S.ntodo = 0;
     S.nin = 0;
     advance(S, tab);
+    S.peek.gave_up = 0;
     peek(S);
 }
 
@@ -269,7 +270,14 @@ __global__ __launch_bounds__(kCommitT) void k_search_commit(SearchState* __restr
     for (int x = threadIdx.x; x < words; x += kCommitT) to[x] = from[x];
     load_log2_table(tab);
     __syncthreads();
-    if (threadIdx.x == 0) {
+    const bool gave_up = m == 1 && res[3] == -(double)kSweepGaveUp;  // uniform
+    if (gave_up) {  // no point; the same solve comes again by the sweep
+        if (threadIdx.x == 0) {
+            slot[0] = -1;
+            S.peek.gave_up = S.todo[S.nin] == 0.0 ? 1 : 2;
+            if (peek_out) *peek_out = S.peek;
+        }
+    } else if (threadIdx.x == 0) {
         // points for todo[nin .. nin+m), in query order
         for (int g = 0; g < m; g++) {
             slot[g] = -1;
@@ -292,6 +300,7 @@ __global__ __launch_bounds__(kCommitT) void k_search_commit(SearchState* __restr
             finish(S);
         else if (S.nin >= S.ntodo)
             advance(S, tab);  // the pass's solves are all in
+        S.peek.gave_up = 0;
         peek(S);
         if (peek_out) *peek_out = S.peek;
     }

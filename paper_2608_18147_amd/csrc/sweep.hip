@@ -927,7 +927,7 @@ __global__ __launch_bounds__(64) void k_sweep_pick(SweepArgs a, int32_t exact_s,
     const int64_t p = a.H.p;
     if (a.K[a.nblk] != 0) {
         if (lane == 0) {
-            st[0] = 0;
+            st[0] = a.K[a.nblk] == kSweepGaveUp ? -kSweepGaveUp : 0;
             out[0] = __builtin_huge_val();
         }
         return;
@@ -1087,10 +1087,11 @@ __global__ __launch_bounds__(kTrT1) void k_sweep_finish(SweepArgs a, int32_t exa
     const int tid = threadIdx.x, lane = tid % kSB, wave = tid / kSB;
     const int64_t p = a.H.p;
     load_log2_table(tab);
-    if (a.K[a.nblk] != 0) {  // uniform: a failed solve
+    if (a.K[a.nblk] != 0) {  // uniform: a failed solve, or one given up
         if (tid == 0) {
             out[0] = __builtin_huge_val();
-            out[1] = out[2] = out[3] = 0.0;
+            out[1] = out[2] = 0.0;
+            out[3] = a.K[a.nblk] == kSweepGaveUp ? -(double)kSweepGaveUp : 0.0;
         }
         return;
     }
@@ -1346,20 +1347,23 @@ size_t sweep_scratch_bytes(int64_t d) {
 
 size_t sweep_cost_bytes() { return (size_t)kQAll * sizeof(double); }
 
-// Above these sizes the layers with bounds (launch_layers) take the sweep's
-// place: their launches (one per layer, 5 - 10 us when little is left to
-// evaluate) cost more than the sweep's chain of blocks while there are few
-// values for each layer.  Sweep against layers: 4999 values, 16 layers 0.61 /
-// 0.37 ms, 64 layers 1.2 / 1.4 ms; 12 000 values, 200 layers 6.0 / 6.3 ms;
-// 24 000, 64 layers 5.9 / 3.2 ms; 2^18, 32 layers 134 / 7.9 ms.
-constexpr int64_t kLayersMinP = kHeldMaxP;
-constexpr int64_t kLayersPerLayer = 64;
+// Above these sizes the layers with bounds (launch_layers) take the sweep's place: a layer's
+// launch takes 20 us at least, so few values for each layer are solved faster by
+// the sweep's chain of blocks.  Sweep / layers in ms on normal values (lambda 0.01, 0.3; at
+// lambda = 0 the layers are faster everywhere): 4097 values, 16 layers 0.54 / 0.32, 0.52 /
+// 0.36, 32 layers 0.80 / 0.70, 0.72 / 0.73; 6000 values, 48 layers 1.34 / 1.21, 1.22 / 1.22, 64
+// layers 1.51 / 1.57, 1.37 / 1.59; 8000 values, 64 layers 1.99 / 1.63, 1.84 / 1.69, 96 layers
+// 2.47 / 2.33, 2.30 / 2.41; 12 000 values, 128 layers 4.44 / 3.71, 4.18 / 3.58; 2^18, 32
+// layers 134 / 8.3.
+bool use_layers(int64_t p, int32_t I) { return p > kHeldMaxP && p > 3072 + 64 * (int64_t)I; }
 
-// Up to kHeldMaxP values the costs fit in registers (launch_held).  Below
-// kHeldMinP values, or few for each layer, the sweep's chain of blocks is shorter than
-// a hand-over between workgroups for every layer.
-constexpr int64_t kHeldMinP = 256;
-constexpr int64_t kHeldPerLayer = 4;
+// Up to kHeldMaxP values the costs fit in registers (launch_held).  With few values in all, or
+// for each layer, the sweep's chain of blocks is as short as a hand-over between workgroups
+// for every layer.  Sweep / held layers in us at lambda = 0.1: 100 values, 32 layers 61 / 67;
+// 257 values, 4 layers 37 / 26, 32 layers 91 / 80, 128 layers 183 / 180, 200 layers 250 /
+// 257; 512 values, 128 layers 211 / 183; 1024 values, 200 layers 388 / 274; 4096 values, 4
+// layers 283 / 59, 200 layers 1786 / 720.
+bool use_held(int64_t p, int32_t I) { return p > 256 && p <= kHeldMaxP && p > 4 * (int64_t)I; }
 
 hipError_t launch_sweep(const SweepSolve& S, int32_t exact_s, double* out, int32_t* chain,
                         hipStream_t st) {
@@ -1367,9 +1371,9 @@ hipError_t launch_sweep(const SweepSolve& S, int32_t exact_s, double* out, int32
     const SweepArgs a = make_args(S);
     const int32_t L = a.I - 2;  // recursive layers 3..I
     hipError_t e;
-    if (a.H.p > kLayersMinP && a.H.p > kLayersPerLayer * a.I)
+    if (S.bounds && use_layers(a.H.p, a.I))
         e = launch_layers(S, st);
-    else if (a.H.p <= kHeldMaxP && a.H.p > kHeldMinP && a.H.p > kHeldPerLayer * a.I)
+    else if (use_held(a.H.p, a.I))
         e = launch_held(S, st);
     else if (L <= 8)
         e = sweep_launch<8>(a, st);

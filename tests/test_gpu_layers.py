@@ -151,3 +151,47 @@ def test_layers_on_a_uniform_grid(m, s, kind):
             for kw in (dict(dp_schedule=1), dict(dp_schedule=0, recovery=1)))
         assert i1["p"] > 4096 and i1["p"] > 64 * s, "sizes that take the layers with bounds"
         assert torch.equal(k1, k0) and torch.equal(c1, c0) and i1["mse"] == i0["mse"]
+
+
+@pytest.mark.parametrize("n,s", [(20000, 16), (70000, 24)])
+def test_layers_that_give_up(n, s):
+    """Values over 60 decades leave the bounds nothing to hold: the layers stop and the solve
+    comes again by the sweep.  Each entry point's result against the layer-by-layer
+    schedule, with the next solve enqueued ahead (below 2^16 values) and without."""
+    if not torch.cuda.is_available():
+        pytest.skip("no GPU")
+    x = _wide(n)
+    assert np.unique(x).size > max(4096, 3072 + 64 * s)
+    xd = torch.from_numpy(x).to("cuda")
+
+    def opt(**kw):
+        return ecasq.ecasq_default_options(max_search_passes=4, **kw)
+
+    def same(a, b):
+        assert torch.equal(a[1], b[1]) and torch.equal(a[0], b[0])
+        for k in ("t", "lambda", "mse", "entropy", "entropy_surrogate", "dp_solves", "status"):
+            assert a[2][k] == b[2][k], k
+
+    top = ecasq.ecasq_solve_lagrangian(xd, s, 0.0, options=opt(refine_rounds=0))
+    b = 0.6 * top[2]["entropy_surrogate"]
+    ecasq.ecasq_timing_enable(True)
+    try:
+        print("[case] give up, budget", n, s, b, flush=True)
+        ecasq.ecasq_timing_read(ecasq.TIMING_SWEEP, reset=True)
+        got = ecasq.ecasq_solve(xd, s, b, options=opt())
+        runs = ecasq.ecasq_timing_read(ecasq.TIMING_SWEEP, reset=True)[1]
+        assert got[2]["dp_solves"] > 1 and runs > got[2]["dp_solves"], "a solve has given up"
+        same(got, ecasq.ecasq_solve(xd, s, b, options=opt(dp_schedule=0, recovery=1)))
+        print("[case] give up, fixed multiplier", n, s, flush=True)
+        ecasq.ecasq_timing_read(ecasq.TIMING_SWEEP, reset=True)
+        got = ecasq.ecasq_solve_lagrangian(xd, s, 0.01, options=opt())
+        assert ecasq.ecasq_timing_read(ecasq.TIMING_SWEEP, reset=True)[1] == 2
+        same(got, ecasq.ecasq_solve_lagrangian(xd, s, 0.01,
+                                               options=opt(dp_schedule=0, recovery=1)))
+    finally:
+        ecasq.ecasq_timing_enable(False)
+    print("[case] give up, two budgets", n, s, flush=True)
+    two = [ecasq.ecasq_solve_budgets(xd, s, [b, 0.8 * b], options=opt(**kw))
+           for kw in ({}, dict(dp_schedule=0, recovery=1))]
+    for a, b in zip(*two):
+        same(a, b)

@@ -105,7 +105,10 @@ DP_CASES = [
     ("dups_700", 700, 10, 0.3),
     ("wide_range_2000", 2000, 10, 0.1),  # interval widths from 2^-148 to 2^128
     ("normal_190_s9", 190, 9, 0.1),      # three column blocks: one sweep step, a short chain
-    ("normal_4500_s64", 4500, 64, 0.02),  # two layer groups, 71 column blocks
+    # two layer groups, 71 column blocks: the sweep (above 4096 values only where they are
+    # few for each layer; from 257 to 4096 the layers held in registers, weights_5000 the
+    # layers with bounds)
+    ("normal_4500_s64", 4500, 64, 0.02),
 ]
 
 
@@ -150,7 +153,8 @@ def _random_shape(seed):
     """A seeded (input, s, lambda) with d from 65 to 2600 (ragged column
     blocks), s in one of the sweep's layer-group ranges (up to 10, 11 to 18,
     19 to 40 with s = 32 among them, 41 to 70: two groups) and lambda = 0 one
-    time in four."""
+    time in four.  Above 256 values these are solved by the layers held in
+    registers (but those of few values for each layer)."""
     rng = np.random.default_rng(1000 + seed)
     d = int(rng.integers(65, 2601))
     lo, hi = [(3, 10), (11, 18), (19, 40), (41, 70)][seed % 4]
@@ -162,7 +166,7 @@ def _random_shape(seed):
 
 @pytest.mark.parametrize("seed", range(12))
 def test_sweep_layers_random_shapes(seed):
-    """Every layer's values and argmins of the sweep bit for bit against the
+    """Every layer's values and argmins of schedule 1 bit for bit against the
     oracle's dumped DP, on seeded random sizes, layer counts, multipliers
     and input kinds."""
     name, d, s, lam = _random_shape(seed)
@@ -242,14 +246,12 @@ def _sample_cols(rng, lo, p, n):
                                              ("weights_256k", 16, 0.1)],
                          ids=["weights_256k_s32", "student_t_1m_s64", "weights_256k_s16"])
 def test_full_size_sweep_sampled(workload, s, lam):
-    """Full-size inputs, DP schedule 1 (the column-block sweep) at one
+    """Full-size inputs, DP schedule 1 (here the layers with bounds) at one
     multiplier: every layer checked bit for bit at sampled columns against the
     oracle's recomputation from the GPU's previous layer.  At 2^18 also the
     recomputed argmins and the accumulators along them; at 2^20 (s = 64) the
-    values the sweep keeps (recomputing every argmin there is a full
-    layer-by-layer solve).  These sizes run the early steps that make two
-    diagonal blocks final per launch, with one (s = 16, 32) and two (s = 64)
-    layer groups."""
+    values that are kept (recomputing every argmin there is a full
+    layer-by-layer solve)."""
     x = inputs.make(workload, seed=0)
     full = x.size <= (1 << 18)
     _say("full-size sweep trace", workload, x.size, s, lam, "argmins" if full else "values")
@@ -278,6 +280,51 @@ def test_full_size_sweep_sampled(workload, s, lam):
             Fo, _, _, _ = pipeline.dp_columns(H, i, lamp, F[i - 1], z, z, cols)
         np.testing.assert_array_equal(F[i, cols], Fo, err_msg=f"F layer {i}")
     last = [F[i, p - 1] for i in range(2, imax + 1)]
+    assert int(out[3]) == 2 + int(np.argmin(last)) and out[0] == min(last)
+
+
+def _decades(d):
+    """Values over 60 decades: no bound holds, and the layers with bounds give the
+    solve up to the sweep."""
+    rng = np.random.default_rng(4)
+    return (rng.standard_normal(d) * 10.0 ** rng.integers(-30, 30, d)).astype(np.float32)
+
+
+@pytest.mark.parametrize("name,d,s,lam", [
+    ("normal", 4500, 80, 0.02), ("normal", 4500, 80, 0.0), ("lognormal", 6000, 128, 0.1),
+    ("normal", 12000, 200, 0.1), ("decades", 40000, 24, 0.01), ("decades", 1 << 18, 32, 0.1),
+    ("decades", 1 << 18, 32, 0.0)])
+def test_sweep_of_many_blocks(name, d, s, lam):
+    """The column-block sweep over several launches: the tiles that add earlier launches'
+    blocks (four, two and one wavefronts to a column block), helpers and the hand-over
+    between launches, in one and several layer groups.  Every layer's values at sampled
+    columns bit for bit against the oracle's recomputation from the previous layer."""
+    x = _decades(d) if name == "decades" else _dp_input(name, d)
+    _say("sweep of many blocks", name, d, s, lam)
+    H = pipeline.prepare(x)
+    p = H.p
+    assert p > 4096
+    ecasq.ecasq_timing_enable(True)
+    try:
+        xd = _dev(x)
+        ecasq.ecasq_timing_read(ecasq.TIMING_SWEEP, reset=True)
+        F, _, _, _, out = ecasq.ecasq_dp_trace(xd, s, lam, schedule=1, argmins=False)
+        runs = ecasq.ecasq_timing_read(ecasq.TIMING_SWEEP, reset=True)[1]
+    finally:
+        ecasq.ecasq_timing_enable(False)
+    # by its size, or after the layers with bounds gave up
+    assert runs == (2 if name == "decades" else 1) and (runs == 2 or p <= 3072 + 64 * s)
+    F = F.cpu().numpy()
+    rng = np.random.default_rng(322)
+    z = np.zeros(F.shape[1])
+    for i in range(2, s + 1):
+        cols = _sample_cols(rng, i - 1, p, 8)
+        cols = np.unique(np.concatenate([cols, [c for c in (1023, 1024, 1025, 4095, 4096)
+                                                if i - 1 <= c < p]])).astype(np.int64)
+        Fo = (pipeline.dp_columns(H, 2, lam * H.s2tot, cols=cols) if i == 2 else
+              pipeline.dp_columns(H, i, lam * H.s2tot, F[i - 1], z, z, cols))[0]
+        np.testing.assert_array_equal(F[i, cols], Fo, err_msg=f"F layer {i}")
+    last = [F[i, p - 1] for i in range(2, s + 1)]
     assert int(out[3]) == 2 + int(np.argmin(last)) and out[0] == min(last)
 
 
