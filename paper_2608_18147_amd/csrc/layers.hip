@@ -120,19 +120,22 @@ __device__ __forceinline__ bool live(LayArgs& a) {
 }
 
 // The steps up to layer i at whose rate the layers after it would take as long as the whole
-// solve by the sweep, and a twentieth of the sweep's time on top for layers that need more than
-// the rest.  In microseconds: the sweep's time (a chain of blocks for few values, cells at a
+// solve by the sweep, and some on top for layers that need more than the rest: a twentieth of
+// the sweep's time, and what a column far from all others (the last of a heavy tail) takes
+// by itself.  In microseconds: the sweep's time (a chain of blocks for few values, cells at a
 // rate for many: 5000 values and 16 layers 0.58 ms, 16384 and 32 2.6, 128 5.6, 65536 and 32
-// 13.2, 2^18 and 32 132 and 95 at lambda = 0), a layer with few steps, and 0.18 for a step (0.166 to 0.184 from
-// inputs with 1000 to 5000 steps of a wavefront in a layer; half at lambda = 0).
+// 13.2, 2^18 and 32 132 and 95 at lambda = 0), a layer with few steps, and 0.18 for a step
+// (0.166 to 0.184 from inputs with 1000 to 5000 steps of a wavefront in a layer; half at
+// lambda = 0).
 __device__ __forceinline__ uint32_t work_limit(int64_t p, int32_t I, int32_t i, bool zero) {
-    const double n = (double)p, left = (double)(I - i);
+    const double n = (double)p, left = (double)(I - i), step = zero ? 0.09 : 0.18;
     if (left < 1.0) return 0xFFFFFFFFu;
     const double sweep =
         n * __builtin_fmax(0.08 + 0.002 * I + 7e-7 * n, (zero ? 4.4e-8 : 6.2e-8) * n * I);
     const double layer = 18.0 + n / 1500.0;
-    const double us = 0.05 * sweep + (double)(i - 2) * __builtin_fmax(0.0, sweep / left - layer);
-    return (uint32_t)__builtin_fmin(us / (zero ? 0.09 : 0.18), 4e9);
+    const double alone = n / (p < kWideP ? 16.0 : 8.0);
+    const double rest = (double)(i - 2) * __builtin_fmax(0.0, sweep / left - layer);
+    return (uint32_t)__builtin_fmin(__builtin_fmax(0.05 * sweep / step, alone) + rest / step, 4e9);
 }
 
 __device__ __forceinline__ LayWork* work_of(const LayArgs& a) {
