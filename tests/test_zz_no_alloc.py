@@ -1,7 +1,9 @@
 """The allocation-free rounding entry point (ecasq_quantize_noalloc) against
 ecasq_quantize through the C ABI: symbols, counts and entropy bit for bit, on
-two calls in a row, the second with a smaller input and codebook (so counts
-left in the shared device array by the first call would show)."""
+calls in a row, with smaller and larger inputs and codebooks (so counts left in
+the shared device array by an earlier call would show).  Up to 32768 entries one
+workgroup counts by itself and the array is not used; above, every call
+clears and uses it."""
 import numpy as np
 import pytest
 import torch
@@ -37,8 +39,18 @@ def test_noalloc_quantize_matches_quantize_twice():
     _check(inputs.normal(3000, 4), 5, 12)
 
 
-def test_noalloc_quantize_without_hist_and_limits():
-    x = inputs.normal(4097, 5)
+def test_noalloc_clears_the_shared_counts():
+    # all above 32768 entries, through the same array: fewer values, then more
+    # than before, then the same again
+    _check(inputs.student_t(50000, 3), 120, 21)
+    _check(inputs.normal(40001, 4), 5, 22)
+    _check(inputs.normal(32769, 6), 250, 23)
+    _check(inputs.normal(32769, 7), 250, 24)
+
+
+@pytest.mark.parametrize("d", [4097, 40001])
+def test_noalloc_quantize_without_hist_and_limits(d):
+    x = inputs.normal(d, 5)
     xd = torch.from_numpy(x).to("cuda")
     cb = _codebook(x, 17)
     s_ref, e_ref, _ = ecasq.ecasq_quantize(xd, cb, 3)
