@@ -164,7 +164,7 @@ double g_ins_lamB = 0.0;  // the multiplier the last search's B was found at
 
 struct Layout {
     size_t v, N, S, S2, gv, gN, gS, gS2, F0, F1, M0, M1, P0, P1, pval, pidx, last, res, mres,
-        small, chain, kstar, prep, swF, swQ, swB, swK, swchain, sstate, schains, two, cres, cchain;
+        small, chain, kstar, prep, swF, swQ, swK, swchain, sstate, schains, two, cres, cchain;
     int64_t pstride;  // partial entries per multiplier
     size_t swKbytes;  // bytes at swK
     size_t total;
@@ -214,7 +214,6 @@ Layout layout(int64_t d, int32_t s, int32_t flags) {
     L.pidx = take(sizeof(int32_t) * np);
     L.swF = take(sweep ? sizeof(double) * (size_t)(s + 1) * (size_t)d : 0);
     L.swQ = take(sweep ? sweep_cost_bytes() : 0);
-    L.swB = take(sweep ? layers_scratch_bytes(d) : 0);
     L.swKbytes = !sweep ? 0
                  : (flags & kWsSweepArgmins) ? sizeof(int32_t) * (size_t)(s + 1) * (size_t)d
                                              : sweep_scratch_bytes(d);
@@ -390,7 +389,6 @@ SweepSolve sweep_args(const Ctx& c) {
     S.H = c.H;
     S.F = c.at<double>(c.L.swF);
     S.Q = c.at<double>(c.L.swQ);
-    S.B = c.at<char>(c.L.swB);
     S.K = c.at<int32_t>(c.L.swK);
     S.kbytes = c.L.swKbytes;
     S.st = c.at<int32_t>(c.L.swchain) + 256;

@@ -146,13 +146,12 @@ hipError_t launch_split(const double* Fw, const double* Bw, int64_t ml, int64_t 
 // layer in tables of I+1 rows of ld entries (rows 2..I used).
 struct SweepSolve {
     Hist H;
-    double* F;
+    double* F;     // rows 0 and 1 hold the scratch of the layers with bounds
     double* Q;     // sweep_cost_bytes(): the next diagonal block's costs
     int32_t* K;    // step counters and traceback scratch; the argmins on request
                    // (launch_sweep_argmins), when it holds (I + 1) x ld int32
     size_t kbytes = 0;  // bytes at K
     int32_t* st;   // traceback state, 264 int32
-    char* B;       // layers_scratch_bytes(p)
     int64_t ld;    // >= p
     int32_t I;     // last layer, min(s, p), 2..255
     double lamp;   // lambda' in MSE units (when lampp is null)
@@ -181,8 +180,8 @@ hipError_t launch_sweep_argmins(const SweepSolve& S, hipStream_t st);
 hipError_t launch_sweep_accumulators(const SweepSolve& S, double* M, double* Ph, hipStream_t st);
 
 // ---- layers.hip ----
-// F of layers 2..I by the layers with bounds (p >= 2), in S.B's scratch.
-size_t layers_scratch_bytes(int64_t d);
+// F of layers 2..I by the layers with bounds (p > kHeldMaxP); its scratch is in rows 0
+// and 1 of F, which hold no layer.
 hipError_t launch_layers(const SweepSolve& S, hipStream_t st);
 
 // ---- held.hip ----

@@ -848,13 +848,17 @@ hipError_t launch_all(LayArgs a, hipStream_t st) {
 
 }  // namespace
 
+namespace {
+
 // The work words, the units' end values, then the two rows of lines and of unit-end values (a
-// unit is at least 16 values).
-size_t layers_scratch_bytes(int64_t d) {
-    const size_t nun = (size_t)(d + kGC - 1) / kGC;
+// unit is at least 16 values): 8 bytes a value and a little, where rows 0 and 1 of F have 16.
+size_t scratch_bytes(int64_t p) {
+    const size_t nun = (size_t)(p + kGC - 1) / kGC;
     return kWorkBytes + align256(16 * kUnit * nun) + align256(2 * 16 * nun) +
            align256(2 * 8 * nun);
 }
+
+}  // namespace
 
 hipError_t launch_layers(const SweepSolve& S, hipStream_t st) {
     LayArgs a;
@@ -862,7 +866,8 @@ hipError_t launch_layers(const SweepSolve& S, hipStream_t st) {
     a.F = S.F;
     a.nblk = (S.H.p + kSB - 1) / kSB;
     a.nun = (S.H.p + kGC - 1) / kGC;
-    char* o = S.B + kWorkBytes;
+    if (scratch_bytes(S.H.p) > 2 * sizeof(double) * (size_t)S.ld) return hipErrorInvalidValue;
+    char* o = reinterpret_cast<char*>(S.F) + kWorkBytes;
     a.SB = reinterpret_cast<double2*>(o);
     o += align256(16 * kUnit * (size_t)a.nun);
     a.LN = reinterpret_cast<double2*>(o);

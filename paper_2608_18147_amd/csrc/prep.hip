@@ -444,6 +444,7 @@ __global__ void k_prep_tail(const int64_t* __restrict__ p, const double* __restr
 }  // namespace
 
 size_t prep_scratch_bytes(int64_t d) {
+    if (prep_is_small(d)) return 0;  // (launch_prep_small needs none)
     const int64_t nblk = (d + kSortTile - 1) / kSortTile;
     const int64_t nchunk = (d + kChunk - 1) / kChunk;
     size_t b = 0;
@@ -451,7 +452,6 @@ size_t prep_scratch_bytes(int64_t d) {
     b += align256(sizeof(uint32_t) * 256 * nblk);      // digit histogram
     b += align256(sizeof(uint64_t) * kRec * nchunk);   // chunk records
     b += align256(sizeof(uint64_t) * kRec * ((nchunk + kScanBlock - 1) / kScanBlock));  // runs
-    b += align256(sizeof(uint32_t) * 256);             // digit totals
     return b;
 }
 
@@ -487,8 +487,8 @@ hipError_t launch_prep(const void* x, int dt, int64_t d, void* scratch, hipStrea
     uint64_t* rec = reinterpret_cast<uint64_t*>(w);
     w += align256(sizeof(uint64_t) * kRec * nchunk);
     uint64_t* tot = reinterpret_cast<uint64_t*>(w);
-    w += align256(sizeof(uint64_t) * kRec * ((nchunk + kScanBlock - 1) / kScanBlock));
-    uint32_t* dtot = reinterpret_cast<uint32_t*>(w);
+    // digit totals: the records come after the sort and are larger
+    uint32_t* dtot = reinterpret_cast<uint32_t*>(rec);
 
     const int ig = (int)((d + 255) / 256 < 65536 ? (d + 255) / 256 : 65536);
     if (dt == 0) k_ingest<0><<<ig, 256, 0, st>>>(x, d, k0, flags_dev);

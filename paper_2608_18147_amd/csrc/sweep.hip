@@ -1324,7 +1324,7 @@ size_t counter_bytes(int64_t p) {
 }
 
 bool sweep_ok(const SweepSolve& S) {
-    return S.I >= 2 && S.I <= 255 && S.H.p >= 2 && S.ld >= S.H.p && S.F && S.Q && S.K && S.B && S.st &&
+    return S.I >= 2 && S.I <= 255 && S.H.p >= 2 && S.ld >= S.H.p && S.F && S.Q && S.K && S.st &&
            S.kbytes >= counter_bytes(S.H.p) && S.kbytes >= trace_scratch_bytes(S.H.p);
 }
 

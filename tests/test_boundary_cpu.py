@@ -46,6 +46,25 @@ def test_workspace_size_is_linear_in_d():
     assert extra >= 33 * (1 << 16) * 4
 
 
+@pytest.mark.parametrize("d,s,flags,size", [
+    (1, 2, 0, 1627136),
+    (1024, 16, 2, 48540160),
+    (4096, 64, 2, 50912256),
+    (4097, 16, 0, 16073472),
+    (4097, 16, 2, 49136384),
+    (5000, 16, 6, 49470976),
+    (16384, 32, 1, 61456384),
+    (16384, 32, 2, 53674240),
+    (65537, 255, 2, 187346944),
+    (262144, 32, 2, 132640000),
+    (262144, 32, 0, 922479616),
+    (1048576, 64, 6, 687458048),
+])
+def test_workspace_sizes_only_shrink(d, s, flags, size):
+    """A caller may have stored a workspace's size: what was enough once stays enough."""
+    assert ecasq.ecasq_workspace_size(d, s, flags) <= size
+
+
 def test_argument_errors_before_any_device_work():
     """Argument errors come back synchronously (no GPU is touched)."""
     L = ecasq.lib()
