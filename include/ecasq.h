@@ -13,10 +13,9 @@
  * codebook, refines it with the three-colour pass of Sec. 6, and rounds the
  * input stochastically (Sec. 2) with Philox4x32-10.
  *
- * By default (ecasq_options.dp_schedule = 1) each DP solve is one sweep over
- * column blocks that keeps F of every layer, O(s d) memory (12 (s+1) d bytes),
- * and the codebook is the argmin traceback of the solve it was found in;
- * `recovery` is then ignored.  The layer-by-layer schedule (dp_schedule = 0)
+ * By default (ecasq_options.dp_schedule = 1) each DP solve keeps F of every
+ * layer, O(s d) memory (8 (s+1) d bytes), and the codebook is the argmin
+ * traceback of the solve it was found in; `recovery` is then ignored.  The layer-by-layer schedule (dp_schedule = 0)
  * keeps two O(d) layers, as Sec. 5 states the method, and recovers the
  * codebook with Hirschberg's method in O(d) space (recovery = 0) or from
  * stored argmins (recovery = 1).
@@ -77,9 +76,8 @@ typedef struct {
                                   1 stored argmins.  Ignored by the default sweep
                                   (dp_schedule 1), which traces its argmins back */
     int32_t search_width;      /* multipliers per search pass: 1 (default) or 8 */
-    int32_t dp_schedule;       /* 1: column-block sweep over all layers at once, O(s d)
-                                  space (default); 0: layer by layer, O(d) space (see
-                                  ecasq_solve_ex) */
+    int32_t dp_schedule;       /* 1: F of every layer kept, O(s d) space (default);
+                                  0: layer by layer, O(d) space (see ecasq_solve_ex) */
     int32_t alphabet;          /* permissible values P (App. D): 0 the distinct input
                                   values, P = X (default); 1 a uniform grid of
                                   alphabet_size points over [min X, max X]; 2 the input
@@ -110,7 +108,9 @@ typedef struct {
     double rate_total;        /* H(Xhat) + 32 t / d (App. F.1 rate accounting) */
     int32_t dp_solves;        /* full DP solves (multipliers) run by the search */
     int32_t refine_rounds_run;
-    int64_t cells;            /* DP cells evaluated (search + recovery) */
+    int64_t cells;            /* DP cells of the programs solved (search + recovery):
+                                 every (column, predecessor, layer), also where a
+                                 schedule needs to evaluate only a part of them */
     int32_t status;           /* ecasq_status of the solve */
     int32_t search_passes;    /* passes of the budget search (0 in fixed-lambda mode) */
 } ecasq_info;
@@ -171,14 +171,21 @@ ecasq_status ecasq_solve(const void *x, ecasq_dtype dt, int64_t d, int32_t s,
  *   0  layer by layer with two rolling layers of O(p) memory, as Sec. 5 states
  *      it; the codebook is recovered by Hirschberg's method (recovery 0) or
  *      from stored argmins (recovery 1);
- *   1  one sweep over column blocks in which the interval cost and entropy
- *      term of each cell serve every layer; keeps F of all layers, 8 (s+1) d
- *      bytes, 48 MB of per-launch cost tables and partial minima (any d),
- *      and about d bytes of step counters and traceback scratch
- *      (an int32 argmin table of F's shape only when an inspection call asks
- *      for argmins or accumulators).  The
- *      codebook comes from the argmin traceback of the solve it was found
- *      in, each argmin recomputed from the kept layers (recovery is
+ *   1  F of all layers kept, 8 (s+1) d bytes, with 48 MB of per-launch cost
+ *      tables and partial minima (any d) and about d bytes of step counters and
+ *      traceback scratch (an int32 argmin table of F's shape only when an
+ *      inspection call asks for argmins or accumulators).  By the number of
+ *      values p and of layers I = min(s, p) it is solved
+ *        - with every cost held in registers, formed once (256 < p <= 4096,
+ *          p > 4 I);
+ *        - layer by layer with bounds that leave only predecessors that may hold
+ *          a minimum to evaluate (p > 4096, p > 3072 + 64 I; a solve whose
+ *          prefix sums cancel so far that the bounds hold nothing is
+ *          stopped and solved by the sweep);
+ *        - by one sweep over column blocks in which the interval cost and
+ *          entropy term of each cell serve every layer (all others).
+ *      The codebook comes from the argmin traceback of the solve it was
+ *      found in, each argmin recomputed from the kept layers (recovery is
  *      ignored). */
 ecasq_status ecasq_solve_ex(const void *x, ecasq_dtype dt, int64_t d, int32_t s,
                             double bits_per_entry, const ecasq_options *opts, void *stream,
@@ -373,6 +380,16 @@ ecasq_status ecasq_solve_batched(const void *x, ecasq_dtype dt, int64_t n, int64
  * (0 when d < 1, s < 2 or flags outside 0..7). */
 size_t ecasq_workspace_size(int64_t d, int32_t s, int32_t flags);
 
+/*
+ * Memory kept between calls.  The solves (without a caller workspace, and the
+ * optimal DP's tables in any case) and ecasq_encode take device memory from a pool of the
+ * library's own, one per device, which keeps up to 2 GiB when they return;
+ * the solves also keep up to 8 pinned host blocks of 64 KB with two events
+ * each.  Other allocators cannot use what is kept: ecasq_trim gives back, on every
+ * device, all that no call in progress holds (later calls take it anew).
+ */
+ecasq_status ecasq_trim(void);
+
 /* Static string for a status code. */
 const char *ecasq_status_string(ecasq_status st);
 
@@ -448,8 +465,9 @@ int32_t ecasq_inspect_results(double *lams, int32_t *chains, int32_t cap);
  * Launches are kept apart by variant: 0 = one multiplier per launch (fixed
  * lambda, width-1 search, recovery half-DPs), 1 = the 8 multipliers of a
  * search pass, 2 = a whole solve of DP schedule 1 (all its launches, from
- * the table fill to eq. apx_final, timed as one unit; cells counted as for
- * schedule 0), 3 = one layer of the optimal DP (cells = its (k, l, j)
+ * the first to eq. apx_final, timed as one unit; one that is stopped and
+ * solved again by the sweep counts twice; cells are every cell of the program,
+ * as for schedule 0, also where only a part of them is evaluated), 3 = one layer of the optimal DP (cells = its (k, l, j)
  * candidates), 4 = one launch of ecasq_solve_batched (cells not counted).
  * ecasq_timing_read returns, for one variant, the summed milliseconds, the
  * number of timed launches and the (column, predecessor) cells those launches

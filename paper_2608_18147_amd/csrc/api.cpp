@@ -28,23 +28,24 @@ using namespace ecasq;
 namespace {
 
 // Device memory of a solve comes from a pool of the library's own, one per
-// device, that keeps up to kPoolKeep between calls (0.7% of the card) and gives
-// what is above it back when a call ends.  The device's default pool keeps
-// nothing: mapping and unmapping 136 MB took 0.4 ms of each call, and the 1.4 GB of an
-// optimal solve up to 20 ms.  Allocation and release are ordered by the
-// stream, so calls on several threads and streams share the pool; where it cannot
-// be made or is out of memory, what it keeps is given back and the default pool is used.
+// device, that keeps up to kPoolKeep between calls (0.7% of the card), gives
+// what is above it back when a call ends and the rest in ecasq_trim.  The device's
+// default pool keeps nothing: where the process has nothing else in it, mapping and
+// unmapping 136 MB took 0.4 ms of each call, and the 1.4 GB of an optimal solve 20 to 30
+// ms.  Allocation and release are ordered by the stream, so calls on several threads
+// and streams share the pool; where it cannot be made or is out of memory, what it keeps is
+// given back and the default pool is used.
 constexpr uint64_t kPoolKeep = (uint64_t)2 << 30;
+constexpr int kMaxDev = 64;
+std::mutex g_pool_mu;
+hipMemPool_t g_pool[kMaxDev] = {};
+bool g_pool_done[kMaxDev] = {};
 
 hipMemPool_t solve_pool(int dev) {
-    constexpr int kMaxDev = 64;
-    static std::mutex mu;
-    static hipMemPool_t pool[kMaxDev] = {};
-    static bool done[kMaxDev] = {};
     if (dev < 0 || dev >= kMaxDev) return nullptr;
-    std::lock_guard<std::mutex> lock(mu);
-    if (!done[dev]) {
-        done[dev] = true;
+    std::lock_guard<std::mutex> lock(g_pool_mu);
+    if (!g_pool_done[dev]) {
+        g_pool_done[dev] = true;
         hipMemPoolProps props;
         std::memset(&props, 0, sizeof props);
         props.allocType = hipMemAllocationTypePinned;
@@ -54,13 +55,13 @@ hipMemPool_t solve_pool(int dev) {
         hipMemPool_t p = nullptr;
         if (hipMemPoolCreate(&p, &props) == hipSuccess) {
             if (hipMemPoolSetAttribute(p, hipMemPoolAttrReleaseThreshold, &keep) == hipSuccess)
-                pool[dev] = p;
+                g_pool[dev] = p;
             else
                 (void)hipMemPoolDestroy(p);
         }
         (void)hipGetLastError();
     }
-    return pool[dev];
+    return g_pool[dev];
 }
 
 hipError_t solve_alloc(void** p, size_t bytes, hipStream_t st) {
@@ -91,9 +92,10 @@ struct HostBlock {
         return reinterpret_cast<T*>(mem + off);
     }
 };
-constexpr size_t kHostKeep = 8;
+constexpr int kHostKeep = 8;
 std::mutex g_host_mu;
-std::vector<HostBlock> g_host_free;
+HostBlock g_host_free[kHostKeep];  // the first g_host_n
+int g_host_n = 0;
 
 void host_destroy(HostBlock& b) {
     for (auto& e : b.ev)
@@ -107,10 +109,10 @@ bool host_acquire(HostBlock& b) {
     if (hipGetDevice(&dev) != hipSuccess) return false;
     {
         std::lock_guard<std::mutex> lock(g_host_mu);
-        for (size_t k = 0; k < g_host_free.size(); k++)
+        for (int k = 0; k < g_host_n; k++)
             if (g_host_free[k].dev == dev) {
                 b = g_host_free[k];
-                g_host_free.erase(g_host_free.begin() + (std::ptrdiff_t)k);
+                g_host_free[k] = g_host_free[--g_host_n];
                 return true;
             }
     }
@@ -131,8 +133,8 @@ void host_release(HostBlock& b) {
     if (!b.mem) return;
     {
         std::lock_guard<std::mutex> lock(g_host_mu);
-        if (g_host_free.size() < kHostKeep) {
-            g_host_free.push_back(b);
+        if (g_host_n < kHostKeep) {
+            g_host_free[g_host_n++] = b;
             b = HostBlock();
         }
     }
@@ -1308,6 +1310,23 @@ void ecasq_default_options(ecasq_options* opts) {
 size_t ecasq_workspace_size(int64_t d, int32_t s, int32_t flags) {
     if (d < 1 || s < 2 || flags < 0 || flags > 7) return 0;
     return layout(d, s, flags).total;
+}
+
+ecasq_status ecasq_trim(void) {
+    ecasq_status rc = ECASQ_OK;
+    {
+        std::lock_guard<std::mutex> lock(g_pool_mu);
+        for (hipMemPool_t p : g_pool)
+            if (p && hipMemPoolTrimTo(p, 0) != hipSuccess) rc = ECASQ_EHIP;
+    }
+    HostBlock idle[kHostKeep];
+    int n = 0;
+    {
+        std::lock_guard<std::mutex> lock(g_host_mu);
+        for (; g_host_n > 0; n++) idle[n] = g_host_free[--g_host_n];
+    }
+    for (int k = 0; k < n; k++) host_destroy(idle[k]);
+    return rc;
 }
 
 const char* ecasq_status_string(ecasq_status st) {

@@ -79,7 +79,7 @@ EXPORTS = (
     "ecasq_solve_budgets", "ecasq_solve_optimal", "ecasq_opt_trace",
     "ecasq_solve_timeshare", "ecasq_quantize_timeshare", "ecasq_encode_bound", "ecasq_encode",
     "ecasq_decode", "ecasq_quantize_noalloc", "ecasq_inspect_enable", "ecasq_inspect_points",
-    "ecasq_inspect_results",
+    "ecasq_inspect_results", "ecasq_trim",
 )
 
 
@@ -121,6 +121,7 @@ def lib():
                                       vp, vp]
     L.ecasq_workspace_size.argtypes = [i64, i32, i32]
     L.ecasq_workspace_size.restype = ctypes.c_size_t
+    L.ecasq_trim.argtypes = []
     L.ecasq_status_string.argtypes = [i32]
     L.ecasq_status_string.restype = ctypes.c_char_p
     L.ecasq_histogram.argtypes = [vp, i32, i64, vp, vp, vp, vp, vp, P(i64)]
@@ -140,7 +141,7 @@ def lib():
                  "ecasq_solve_batched", "ecasq_histogram", "ecasq_dp_trace",
                  "ecasq_solve_budgets", "ecasq_solve_optimal", "ecasq_opt_trace",
                  "ecasq_solve_timeshare", "ecasq_quantize_timeshare", "ecasq_encode",
-                 "ecasq_decode", "ecasq_quantize_noalloc"):
+                 "ecasq_decode", "ecasq_quantize_noalloc", "ecasq_trim"):
         getattr(L, name).restype = i32
     _lib = L
     return L
@@ -183,6 +184,11 @@ def ecasq_status_string(status):
 
 def ecasq_workspace_size(d, s, flags=0):
     return int(lib().ecasq_workspace_size(int(d), int(s), int(flags)))
+
+
+def ecasq_trim():
+    """Give back the device memory and pinned blocks that the library keeps between calls."""
+    _raise(lib().ecasq_trim())
 
 
 def ecasq_solve(x, s, bits_per_entry, options=None, stream=None, workspace=None):
