@@ -384,6 +384,9 @@ __global__ __launch_bounds__(256) void k_rans_pack(const uint8_t* __restrict__ s
 // its symbol except in the (at most t) entries that are shared, which go on
 // through c.
 constexpr uint32_t kDShared = 256u;
+// Up to kDFew symbols an entry serves kDFewSlots slots: filling a table of 8 slots an entry takes
+// about 10 us with 256 values (decoding 8 symbols: 75 us a call, 60 with the small table).
+constexpr int kDFew = 32, kDFewSlots = 1024;
 
 template <int SL>
 struct DecBook {
@@ -419,6 +422,14 @@ __device__ __forceinline__ bool load_dec_book(DecBook<SL>& B, const uint8_t* __r
     if (tid == 0) B.sc[0] = 0u;
     __syncthreads();
     uint32_t q = 0, c = 0, e = B.sc[1];
+    if constexpr (SL == kDFewSlots) {  // one entry a thread: its symbol by a search (sc rises
+                                       // up to sc[t] = 2^16)
+#pragma unroll
+        for (uint32_t step = 128; step > 0; step >>= 1)
+            q += B.sc[q + step] <= (uint32_t)(SL * tid) ? step : 0u;
+        c = B.sc[q];
+        e = B.sc[q + 1];
+    }
     for (int b = tid; b < (int)kRM / SL; b += kRT) {
         const uint32_t slot = (uint32_t)(SL * b);
         while (e <= slot) {  // sc[t] = 2^16 ends it
@@ -600,12 +611,13 @@ __global__ __launch_bounds__(kRT) void k_rans_decode(const uint8_t* __restrict__
 // by every lane alike.  From its first state on a segment takes at most two bytes a symbol.
 constexpr int kDSegCap = 2 * kRSeg;
 
+template <int SL>
 __global__ __launch_bounds__(kRT) void k_rans_decode_staged(const uint8_t* __restrict__ in,
                                                             int64_t nin, int64_t d, int32_t t,
                                                             int64_t nseg,
                                                             uint8_t* __restrict__ sym,
                                                             unsigned int* __restrict__ bad) {
-    __shared__ DecBook<8> B;
+    __shared__ DecBook<SL> B;
     __shared__ __align__(16) uint8_t si[kRWaves][kDSegCap + 16];
     __shared__ __align__(16) uint8_t so[kRWaves][kRSeg];
     const int tid = threadIdx.x, lane = tid % 64, wave = tid / 64;
@@ -742,8 +754,10 @@ hipError_t launch_rans_decode(const uint8_t* in, int64_t nin, int64_t d, int32_t
     const int32_t lanes = lanes_of(nseg);
     const int64_t per = (int64_t)lanes * kRWaves;
     const unsigned wg = (unsigned)((nseg + per - 1) / per);
-    if (staged(nseg))
-        k_rans_decode_staged<<<wg, kRT, 0, st>>>(in, nin, d, t, nseg, sym, bad);
+    if (d <= kDFew)
+        k_rans_decode_staged<kDFewSlots><<<wg, kRT, 0, st>>>(in, nin, d, t, nseg, sym, bad);
+    else if (staged(nseg))
+        k_rans_decode_staged<8><<<wg, kRT, 0, st>>>(in, nin, d, t, nseg, sym, bad);
     else
         k_rans_decode<<<wg, kRT, 0, st>>>(in, nin, d, t, lanes, nseg, sym, bad);
     return hipGetLastError();

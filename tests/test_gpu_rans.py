@@ -88,7 +88,7 @@ def test_rans_rejects_malformed_input():
     np.testing.assert_array_equal(back.cpu().numpy(), sym.astype(np.uint8))
 
 
-@pytest.mark.parametrize("d", [1, 15, 16, 17, 4095, 4097, 4 * rans.SEG + 31, 1025 * rans.SEG + 3])
+@pytest.mark.parametrize("d", [1, 15, 16, 17, 32, 33, 4095, 4097, 4 * rans.SEG + 31, 1025 * rans.SEG + 3])
 @pytest.mark.parametrize("t", [2, 5, 256])
 def test_rans_edges(d, t):
     """One symbol to more segments than wavefronts (two to a wavefront), parts
