@@ -1550,7 +1550,7 @@ ecasq_status ecasq_quantize(const void* x, ecasq_dtype dt, int64_t d, const doub
     ECASQ_TRY(check_x(x, dt, d));
     if (!codebook || t < 1 || t > 256 || !symbols || !empirical_entropy) return ECASQ_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (quantize_is_small(d)) {
+    if (quantize_is_small(d, t, false)) {
         HIP_TRY(launch_quantize_small(x, dt, d, codebook, t, seed, symbols, empirical_entropy,
                                       hist, st));
         return ECASQ_OK;
@@ -1572,7 +1572,7 @@ ecasq_status ecasq_quantize_noalloc(const void* x, ecasq_dtype dt, int64_t d,
     ECASQ_TRY(check_x(x, dt, d));
     if (!codebook || t < 1 || t > 256 || !symbols || !empirical_entropy) return ECASQ_EINVAL;
     hipStream_t st = static_cast<hipStream_t>(stream);
-    if (quantize_is_small(d)) {
+    if (quantize_is_small(d, t, true)) {
         HIP_TRY(launch_quantize_small(x, dt, d, codebook, t, seed, symbols, empirical_entropy,
                                       hist, st));
         return ECASQ_OK;

@@ -249,8 +249,9 @@ hipError_t launch_gather(const double* v, const int32_t* u, int32_t t, double* c
 hipError_t launch_quantize(const void* x, int dt, int64_t d, const double* codebook, int32_t t,
                            uint64_t seed, uint8_t* symbols, unsigned long long* hist,
                            hipStream_t st);
-// rounding and entropy in one launch, for d with quantize_is_small(d)
-bool quantize_is_small(int64_t d);
+// rounding and entropy in one launch, for d and t with quantize_is_small(): for callers that
+// would otherwise allocate counts, or have an array for them (noalloc)
+bool quantize_is_small(int64_t d, int32_t t, bool noalloc);
 hipError_t launch_quantize_small(const void* x, int dt, int64_t d, const double* codebook,
                                  int32_t t, uint64_t seed, uint8_t* symbols, double* ent,
                                  int64_t* hist_out, hipStream_t st);

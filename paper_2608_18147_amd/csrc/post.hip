@@ -695,17 +695,22 @@ hipError_t launch_gather(const double* v, const int32_t* u, int32_t t, double* c
     return hipGetLastError();
 }
 
-// One workgroup up to here: a call of 4096 to 20000 entries takes 14 us (16 with 256
-// values), one through the counts' allocation, a second launch and the release
-// 30 us.
+// One workgroup up to here: a call of 4096 entries takes 14 us, of 20000 14 to 18 and of 32768 14
+// to 25 (2 to 256 values), one through the counts' allocation, a second launch and the
+// release 30 to 43.  Without an allocation the three launches take 15 us up to 200000 entries;
+// one workgroup takes 9 + (1.2 to 2.6 us, with the steps of the bracket's search) for each 4096
+// entries above 8192: 15 us at 32768 entries and 2 values, 24576 and 32, 16384 and 256.
 constexpr int64_t kQSmall = 32 * kQT;
 
-bool quantize_is_small(int64_t d) { return d <= kQSmall; }
+bool quantize_is_small(int64_t d, int32_t t, bool noalloc) {
+    const int64_t steps = 32 - __builtin_clz((unsigned)t);  // 2 to 9 from 2 to 256 values
+    return d <= kQSmall && (!noalloc || d * (4 + steps) <= 13 * 16 * kQT);
+}
 
 hipError_t launch_quantize_small(const void* x, int dt, int64_t d, const double* codebook,
                                  int32_t t, uint64_t seed, uint8_t* symbols, double* ent,
                                  int64_t* hist_out, hipStream_t st) {
-    if (!quantize_is_small(d)) return hipErrorInvalidValue;
+    if (d > kQSmall) return hipErrorInvalidValue;
     const uint32_t k0 = (uint32_t)seed, k1 = (uint32_t)(seed >> 32);
     if (dt == 0)
         k_quantize_small<0><<<1, kQT, 0, st>>>(x, d, codebook, t, k0, k1, symbols, ent, hist_out);

@@ -1,9 +1,9 @@
 """The allocation-free rounding entry point (ecasq_quantize_noalloc) against
 ecasq_quantize through the C ABI: symbols, counts and entropy bit for bit, on
 calls in a row, with smaller and larger inputs and codebooks (so counts left in
-the shared device array by an earlier call would show).  Up to 32768 entries one
-workgroup counts by itself and the array is not used; above, every call
-clears and uses it."""
+the shared device array by an earlier call would show).  Up to 16384 entries (32768
+with few values) one workgroup counts by itself and the array is not used; above,
+every call clears and uses it."""
 import numpy as np
 import pytest
 import torch
@@ -40,12 +40,15 @@ def test_noalloc_quantize_matches_quantize_twice():
 
 
 def test_noalloc_clears_the_shared_counts():
-    # all above 32768 entries, through the same array: fewer values, then more
-    # than before, then the same again
+    # through the same array: fewer values, then more than before, then the same again
     _check(inputs.student_t(50000, 3), 120, 21)
     _check(inputs.normal(40001, 4), 5, 22)
     _check(inputs.normal(32769, 6), 250, 23)
     _check(inputs.normal(32769, 7), 250, 24)
+    _check(inputs.normal(16385, 8), 256, 25)
+    # and by one workgroup at its limits: 13 * 16384 / (4 + steps of the search) entries
+    for n, t in ((16384, 256), (23665, 31), (23666, 31), (32768, 3)):
+        _check(inputs.normal(n, 9), t, 26)
 
 
 @pytest.mark.parametrize("d", [4097, 40001])
