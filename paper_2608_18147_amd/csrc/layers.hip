@@ -43,16 +43,18 @@
 // and D by 2^-20 and their rates by 2^-18 of themselves (the approximate
 // reciprocal is good to 2^-24) plus the error 2^-44 (vm N + sqrt(N S2)) of tu and
 // td over the width, and lower the 32-bit h by 2^-18 of itself and 2^-20 y
-// (v_log_f32 is good to about an ulp).
+// (v_log_f32 is good to about an ulp).  Where sums cancel that error may exceed 1:
+// computed frequencies then pass 1, h is negative there, and so are the bounds.
 //
-// What bounds it: the latency of a workgroup's stages (about 20 - 35 us a layer
-// at 2^18 values, four workgroups of four wavefronts on a CU) and, at small
-// multipliers, the FP64 rate of the evaluations left.  2^18 weight-like values, 32
-// layers: 5.3 ms at lambda = 0, 11.7 at 0.01, 7.9 at 0.1 to 1, where the sweep
-// over all pairs takes 97 and 134 ms; of the p^2 / 2 pairs of a layer 0.015%
-// to 0.2% are evaluated and 0.05% to 1% tested one by one.  Bounds that are
-// constant over a unit (no lines) left 1% to 3% and took twice to three times
-// as long.
+// What bounds it: the latency of a workgroup's stages, about 30 us a layer at 16384
+// values (1024 workgroups, of which 768 fit the chip at once: three wavefronts a SIMD at 139 to
+// 146 registers), and with many values the work left: 160 us a layer at 2^18 at lambda = 0, 240
+// above, where VALU issue is 45% used and wavefronts wait half of their time for data
+// or at barriers.  2^18 weight-like values, 32 layers: 5.6 ms at lambda = 0, 12.2 at 0.01,
+// 8.6 at 0.1 to 2, where the sweep over all pairs takes 95 and 132 ms; of the p^2 / 2
+// pairs of a layer 0.03% to 0.2% are evaluated and 0.05% to 1% tested one by one.  Bounds
+// that are constant over a unit (no lines) left 1% to 3% and took twice to three
+// times as long.
 #include "device.hpp"
 #include "launch.hpp"
 

@@ -1066,10 +1066,10 @@ __global__ __launch_bounds__(kSB) void k_sweep_sums(SweepArgs a, const int32_t* 
 // argmin of the chain column's candidates (the same (value, k) pairs as the
 // two kernels above, reduced lexicographically: a butterfly per wavefront,
 // then across the wavefronts).  F_i[j] is known, the least candidate: one
-// whose F_{i-1}[k] + C alone lies above it is not evaluated (the operations
-// are monotone, and -P >= -2^-20: U + D <= d, and the rounding of U / d and D / d is
-// below 2^-53 |v_j| / (v_j - v_k) <= 2^-28 for 24-bit values), which leaves a
-// few.  The thread's predecessors (p <= kTrT1 kTrR1) stay in registers, those of F_{i-2} are
+// whose F_{i-1}[k] + C alone lies above it by 2^-17 lambda' is not evaluated, which leaves
+// a few (the operations are monotone, and -P > -2^-18 where both computed frequencies are
+// at most 1 + 2^-20, which is tested: exact ones are at most 1, but prefix sums may
+// cancel, and a grid's steps may lie far below an ulp of its values).  The thread's predecessors (p <= kTrT1 kTrR1) stay in registers, those of F_{i-2} are
 // loaded while layer i is reduced, and the chosen predecessor's own thread
 // hands out its values for the next layer.
 constexpr int kTrT1 = 1024;
