@@ -5,9 +5,9 @@ One step = the whole path on one synthetic vector already resident in HBM:
 sort + histogram + exact prefix sums, the lambda search (one full dp_APX solve
 per query), codebook recovery, three-colour refinement (5 rounds at most) and
 the final Philox stochastic rounding with its empirical entropy.  By default
-the library's own defaults run: DP schedule 1 (the column-block sweep, every
-layer updated from each cell, codebook from the argmin traceback) with the
-sequential chord search; --dp-schedule 0 runs the layer-by-layer O(d) path
+the library's own defaults run: DP schedule 1 (by size the layers with bounds, the
+layers held in registers or the column-block sweep, codebook from the argmin
+traceback) with the sequential chord search; --dp-schedule 0 runs the layer-by-layer O(d) path
 with the search in passes of 8 multipliers and Hirschberg recovery.
 
 Default workload (weights_256k): fp32, d = 2^18, 0.9 Normal(0, 0.01) +
@@ -95,6 +95,13 @@ SWEEP_COUNTER_VALU_BUSY = 0.759
 # and with it the flop fraction this instruction stream can reach
 SWEEP_COUNTER_VALU_INSTS_PER_SOLVE = 5.982e10
 SWEEP_SOURCES = ("sweep.hip", "device.hpp", "launch.hpp", "log2_table.inc")
+# the same of the layers with bounds (profiles/k_layer_weights_256k.md): bytes per
+# launch, and over all launches of the default workload's solves
+LAYER_TRAFFIC_BYTES_PER_LAUNCH = 3.84e7
+LAYER_COUNTER_FP64_TFLOPS = 10.0
+LAYER_COUNTER_VALU_BUSY = 0.455
+LAYER_SHA = "a6e61cc7e82ab264"
+LAYER_SOURCES = ("layers.hip", "device.hpp", "launch.hpp", "log2_table.inc")
 # the (workload, s) both traffic figures were measured on; null for others
 TRAFFIC_WORKLOAD = ("weights_256k", 32)
 
@@ -132,61 +139,81 @@ def sweep_issue_bound_frac(flops):
     return flops / t_min / 1e12 / FP64_VECTOR_PEAK_TFLOPS
 
 
+def schedule_kernel(p, s):
+    """The kernel that schedule 1 takes for p values and s (the library's rule) and its
+    launches in one solve."""
+    I = min(s, p)
+    if p > 4096 and p > 3072 + 64 * I:
+        return "k_layer", I - 1  # and k_layer_base
+    if 256 < p <= 4096 and p > 4 * I:
+        return "k_held", 2       # and k_held_base
+    return "k_sweep_step", sweep_launches(p, s)
+
+
 def sweep_roofline(p, s, ms, solves, cells, measured=True):
-    """Roofline of DP schedule 1: all k_sweep_step launches of one solve timed
-    as one unit.  achieved = algorithmic FP64 flops per solve (FLOPS_PAIR per
-    (k, j) pair, FLOPS_CELL per (k, j, layer) cell of layers 3..I,
-    FLOPS_LAYER2_COL per layer-2 column) / seconds per solve, against the
-    78.6 TFLOP/s FP64 vector peak.  Also reported, under their own names: the
-    algorithmic FP64 lane operations per second against the lane issue rate
-    (19 per pair with the cost Q, 2 per cell, 20 per layer-2 column; every
-    add, mul, fma, min, max, division and log2 counting 1), and the
-    hardware-counted FP64 rate and VALU busy share of the committed profile
-    (for the kernel sources it was taken on)."""
+    """Roofline of DP schedule 1: all launches of one solve timed as one unit.
+    achieved = algorithmic FP64 flops per solve (FLOPS_PAIR per (k, j) pair,
+    FLOPS_CELL per (k, j, layer) cell of layers 3..I, FLOPS_LAYER2_COL per
+    layer-2 column) / seconds per solve, against the 78.6 TFLOP/s FP64 vector
+    peak.  Also reported, under their own names: the algorithmic FP64 lane
+    operations per second against the lane issue rate (19 per pair with the
+    cost Q, 2 per cell, 20 per layer-2 column; every add, mul, fma, min, max,
+    division and log2 counting 1), and the hardware-counted FP64 rate and VALU
+    busy share of the committed profile (for the kernel sources it was taken
+    on).  The layers with bounds evaluate a small part of the cells: they have no
+    achieved rate in these units, only the counters' (null: no share of the peak
+    is known for these sources)."""
     I = min(s, p)
     pairs = p * (p - 1) / 2.0
     layer_cells = sum((p - i + 1) * (p - i + 2) / 2.0 for i in range(3, I + 1))
     flops = FLOPS_PAIR * pairs + FLOPS_CELL * layer_cells + FLOPS_LAYER2_COL * (p - 1)
     ops = (OPS_PAIR + OPS_Q) * pairs + OPS_CELL * layer_cells + 20.0 * (p - 1)
     per_ms = ms / max(solves, 1)
-    achieved = flops / (per_ms * 1e-3) / 1e12 if ms > 0 else 0.0
-    lane = ops / (per_ms * 1e-3) / 1e12 if ms > 0 else 0.0
-    steps = sweep_launches(p, s)
-    current = measured and kernel_sources_sha(SWEEP_SOURCES) == SWEEP_TRAFFIC_SHA
-    # the library's rule: above 4096 values and 64 per layer a launch per layer
-    # evaluates only predecessors that may hold a minimum
-    bounded = p > 4096 and p > 64 * I
-    if bounded:
-        steps = I - 1
+    kernel, steps = schedule_kernel(p, s)
+    partly = kernel == "k_layer"  # not every cell is evaluated
+    achieved = lane = None
+    if not partly:
+        achieved = flops / (per_ms * 1e-3) / 1e12 if ms > 0 else 0.0
+        lane = ops / (per_ms * 1e-3) / 1e12 if ms > 0 else 0.0
+    measured = measured and kernel != "k_held"
+    if partly:
+        current = measured and kernel_sources_sha(LAYER_SOURCES) == LAYER_SHA
+        traffic = LAYER_TRAFFIC_BYTES_PER_LAUNCH
+        counters = {"fp64_tflops": LAYER_COUNTER_FP64_TFLOPS,
+                    "frac_of_fp64_peak": LAYER_COUNTER_FP64_TFLOPS / FP64_VECTOR_PEAK_TFLOPS,
+                    "valu_busy": LAYER_COUNTER_VALU_BUSY}
+    else:
+        current = measured and kernel_sources_sha(SWEEP_SOURCES) == SWEEP_TRAFFIC_SHA
+        traffic = SWEEP_TRAFFIC_BYTES_PER_LAUNCH
+        counters = {"fp64_tflops": SWEEP_COUNTER_FP64_TFLOPS,
+                    "frac_of_fp64_peak": SWEEP_COUNTER_FP64_TFLOPS / FP64_VECTOR_PEAK_TFLOPS,
+                    "valu_busy": SWEEP_COUNTER_VALU_BUSY,
+                    "frac_at_full_valu_issue": sweep_issue_bound_frac(flops)}
     return {
-        "bound": "alu",
-        "kernel": ("k_layer (fp64 VALU, latency); one DP solve = %d launches" if bounded else
-                   "k_sweep_step (fp64 VALU); one DP solve = %d launches") % steps,
-        "note": ("flops are those of evaluating every cell; the layers with bounds evaluate a "
-                 "small part of them, so achieved and frac compare the solve with a full "
-                 "evaluation and are no share of the hardware's rate" if bounded else None),
+        "bound": "latency" if partly else "alu",
+        "kernel": "%s (fp64 VALU%s); one DP solve = %d launches"
+                  % (kernel, ", latency" if partly else "", steps),
+        "note": ("the layers with bounds evaluate a small part of the cells: flops_per_solve and "
+                 "nominal_cells_per_s are those of a full evaluation, and no rate is formed from them"
+                 if partly else None),
         "achieved": achieved,
         "peak": FP64_VECTOR_PEAK_TFLOPS,
         "unit": "TFLOP/s",
-        "frac": achieved / FP64_VECTOR_PEAK_TFLOPS,
-        "traffic": SWEEP_TRAFFIC_BYTES_PER_LAUNCH if current else None,
+        "frac": None if partly else achieved / FP64_VECTOR_PEAK_TFLOPS,
+        "traffic": traffic if current else None,
         "traffic_unit": "bytes/launch",
         "flops_per_solve": flops,
         "flops_accounting": ("%d per (k, j) pair + %d per (k, j, layer) cell + %d per layer-2 "
                              "column; FMA = 2, division and log2 = 1 each, min/max = 0"
                              % (FLOPS_PAIR, FLOPS_CELL, FLOPS_LAYER2_COL)),
         "lane_ops": {"achieved_tops": lane, "peak_tops": ALU_PEAK_TOPS,
-                     "frac": lane / ALU_PEAK_TOPS, "ops_per_solve": ops},
-        "counters": ({"fp64_tflops": SWEEP_COUNTER_FP64_TFLOPS,
-                      "frac_of_fp64_peak": SWEEP_COUNTER_FP64_TFLOPS / FP64_VECTOR_PEAK_TFLOPS,
-                      "valu_busy": SWEEP_COUNTER_VALU_BUSY,
-                      "frac_at_full_valu_issue": sweep_issue_bound_frac(flops)}
-                     if current else None),
+                     "frac": None if partly else lane / ALU_PEAK_TOPS, "ops_per_solve": ops},
+        "counters": counters if current else None,
         "avg_launch_ms": per_ms / steps,
         "launches": solves * steps,
         "ms_per_solve": per_ms,
         "solves": solves,
-        "cells_per_s": cells / (ms * 1e-3) if ms > 0 else None,
+        "nominal_cells_per_s": cells / (ms * 1e-3) if ms > 0 else None,
     }
 
 
@@ -225,7 +252,7 @@ def cpu_baseline(x, s, lam, sample_d, sample_d1=None):
         "sample": (f"one forward dp_APX solve (s={s}, lambda={lam}) on the {sample_d} smallest "
                    f"entries of the same input: {r['cells']} cells evaluated in {dt:.2f} s "
                    f"on {threads} threads; value counts s*d^2/2 with d={sample_d}"),
-        "exact_cells_per_s": r["cells"] / dt,
+        "nominal_cells_per_s": r["cells"] / dt,
     }
     n1 = sample_d1 or max(1024, sample_d // 4)
     omp.omp_set_num_threads(1)
@@ -235,7 +262,7 @@ def cpu_baseline(x, s, lam, sample_d, sample_d1=None):
         omp.omp_set_num_threads(threads)
     out["one_thread"] = {
         "value": s * n1 * n1 / 2.0 / dt1, "unit": "cell-updates/s", "cores": 1,
-        "exact_cells_per_s": r1["cells"] / dt1,
+        "nominal_cells_per_s": r1["cells"] / dt1,
         "sample": (f"the same solve on the {n1} smallest entries, one thread: "
                    f"{r1['cells']} cells in {dt1:.2f} s"),
     }
@@ -609,6 +636,7 @@ def main():
     ecasq.ecasq_timing_enable(False)
 
     nominal = sum(inf["dp_solves"] * s * d * d / 2.0 for inf, _ in infos)
+    # every cell of each program, evaluated or not
     exact = sum(inf["cells"] for inf, _ in infos)
     value = nominal / elapsed
     info, ent = infos[-1]
@@ -672,7 +700,7 @@ def main():
             "achieved_tops": (flops_per_cell(1) * cells1 / (ms1 * 1e-3) / 1e12
                                 if ms1 > 0 else None),
         },
-        "exact_cells_per_s": exact / elapsed,
+        "nominal_cells_per_s": exact / elapsed,
         "dp_solves_per_step": info["dp_solves"],
         **({"per_budget": info["per_budget"]} if "per_budget" in info else {}),
         "search_passes_per_step": info["search_passes"],

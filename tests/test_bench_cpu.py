@@ -44,14 +44,34 @@ def test_bench_refuses_more_than_one_gpu():
     assert "one GPU" in r.stderr
 
 
-def test_traffic_reported_only_for_its_workload():
-    base = bench.sweep_roofline(261755, 32, 100.0, 1, 1.0, measured=True)
-    other = bench.sweep_roofline(261755, 32, 100.0, 1, 1.0, measured=False)
-    assert other["traffic"] is None
-    if bench.kernel_sources_sha(bench.SWEEP_SOURCES) == bench.SWEEP_TRAFFIC_SHA:
-        assert base["traffic"] == bench.SWEEP_TRAFFIC_BYTES_PER_LAUNCH
+# sizes that the library solves by the layers with bounds, and by the sweep
+@pytest.mark.parametrize("p,s,sources,sha,traffic", [
+    (261755, 32, "LAYER_SOURCES", "LAYER_SHA", "LAYER_TRAFFIC_BYTES_PER_LAUNCH"),
+    (12000, 200, "SWEEP_SOURCES", "SWEEP_TRAFFIC_SHA", "SWEEP_TRAFFIC_BYTES_PER_LAUNCH")])
+def test_traffic_reported_only_for_its_workload(p, s, sources, sha, traffic):
+    base = bench.sweep_roofline(p, s, 100.0, 1, 1.0, measured=True)
+    other = bench.sweep_roofline(p, s, 100.0, 1, 1.0, measured=False)
+    assert other["traffic"] is None and other["counters"] is None
+    if bench.kernel_sources_sha(getattr(bench, sources)) == getattr(bench, sha):
+        assert base["traffic"] == getattr(bench, traffic) and base["counters"] is not None
     else:
-        assert base["traffic"] is None
+        assert base["traffic"] is None and base["counters"] is None
+
+
+def test_no_rate_where_cells_are_left_out():
+    """The layers with bounds evaluate a part of the cells: no fraction of the peak comes
+    from the cells of the whole program."""
+    r = bench.sweep_roofline(261755, 32, 8.0, 1, 1.0, measured=False)
+    assert r["kernel"].startswith("k_layer") and r["launches"] == 31
+    assert r["frac"] is None and r["achieved"] is None and r["lane_ops"]["frac"] is None
+
+
+@pytest.mark.parametrize("p,s,kernel", [
+    (256, 8, "k_sweep_step"), (257, 8, "k_held"), (257, 64, "k_held"), (256, 64, "k_sweep_step"),
+    (4096, 200, "k_held"), (4097, 16, "k_layer"), (4097, 17, "k_sweep_step"),
+    (12000, 139, "k_layer"), (12000, 140, "k_sweep_step")])
+def test_schedule_kernel(p, s, kernel):
+    assert bench.schedule_kernel(p, s)[0] == kernel
 
 
 @pytest.mark.parametrize("p,s", [(5, 3), (17, 8), (70, 40), (200, 32)])
@@ -70,13 +90,11 @@ def test_roofline_flops_are_the_enumerated_cells(p, s):
 
 
 def test_issue_bound_ceiling_covers_the_profiled_rate():
-    """The flop fraction at full VALU issue for the profiled instruction
+    """The sweep's flop fraction at full VALU issue for the profiled instruction
     stream lies above the fraction at the profiled time, by the profiled
     VALU busy share."""
-    p, s = 261755, 32
-    r = bench.sweep_roofline(p, s, 128.35 * 10, 10, 0, measured=True)
-    if r["counters"] is None:
-        pytest.skip("profile constants are for other kernel sources")
-    ceil = r["counters"]["frac_at_full_valu_issue"]
-    assert r["frac"] < ceil < 1.0
-    assert r["frac"] / ceil == pytest.approx(bench.SWEEP_COUNTER_VALU_BUSY, abs=0.01)
+    flops = bench.sweep_roofline(261755, 32, 1.0, 1, 0, measured=False)["flops_per_solve"]
+    frac = flops / 128.35e-3 / 1e12 / bench.FP64_VECTOR_PEAK_TFLOPS
+    ceil = bench.sweep_issue_bound_frac(flops)
+    assert frac < ceil < 1.0
+    assert frac / ceil == pytest.approx(bench.SWEEP_COUNTER_VALU_BUSY, abs=0.01)
