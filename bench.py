@@ -100,7 +100,7 @@ SWEEP_SOURCES = ("sweep.hip", "device.hpp", "launch.hpp", "log2_table.inc")
 LAYER_TRAFFIC_BYTES_PER_LAUNCH = 3.84e7
 LAYER_COUNTER_FP64_TFLOPS = 10.0
 LAYER_COUNTER_VALU_BUSY = 0.455
-LAYER_SHA = "a6e61cc7e82ab264"
+LAYER_SHA = "bfffcf751e7c8ed5"
 LAYER_SOURCES = ("layers.hip", "device.hpp", "launch.hpp", "log2_table.inc")
 # the (workload, s) both traffic figures were measured on; null for others
 TRAFFIC_WORKLOAD = ("weights_256k", 32)

@@ -72,12 +72,13 @@ constexpr int kList = 1024;   // blocks tested per round (those left are listed 
 // of the predecessors where prefix sums cancel so far that no bound holds (values over 60
 // decades, an outlier of 1e18), and then the sweep, which forms each cost once for all
 // layers, is up to ten times faster (2^18 such values, 32 layers: 1390 ms against 132).  So the
-// steps are counted: a workgroup reports its own, between rounds and at its end, once a
-// wavefront has p / 32 of them in a layer (fewer for many layers; most never do), and adds them to
-// a word only where needed, since additions to one word wait for each other, 6 ns each.  When the
-// longest chains of the layers and a kCrowd-th of all steps pass the layer's limit, the
-// solve gives up (the failure word is kSweepGaveUp) and the host takes the sweep: 161 ms in
-// that example, 3.4 against 2.9 for 16384 values.  Counting costs ordinary inputs 0 to 2.5%.
+// steps are counted: a workgroup reports its own, at its end and (64 columns) between
+// rounds, once a wavefront has p / 32 of them in a layer (fewer for many layers; most never
+// do), and adds them to a word only where needed, since additions to one word wait for each
+// other, 6 ns each.  When the longest chains of the layers and a kCrowd-th of all steps pass
+// the layer's limit, the solve gives up (the failure word is kSweepGaveUp) and the host
+// takes the sweep: 161 ms in that example, 3.4 against 2.9 for 16384 values.  Counting costs
+// ordinary inputs 0 to 1.5%.
 struct LayWork {
     unsigned long long all;
     uint32_t chain;       // sum over the layers of the most steps of a wavefront
@@ -726,11 +727,13 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
             __syncthreads();  // the lists are free
             if (tid == 0) {
                 nlist = 0;
-                report();
+                if constexpr (SUP) report();  // (else a layer is short)
             }
             if (tid < CW) nglist[tid] = nclist[tid] = 0;
             __syncthreads();
-            if (stop) return;  // uniform
+            if constexpr (SUP) {
+                if (stop) return;  // uniform
+            }
             uint32_t done = 0;
             for (int x = tid; x < nx; x += T) {
                 const int64_t q = unit(x), dA = q * UN - kA, dB = q * UN - kB;
