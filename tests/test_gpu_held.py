@@ -1,5 +1,6 @@
 """The layers with costs held in registers (schedule 1, up to 4096 distinct values):
-every F_i[j] bit for bit the minimum over all predecessors, at the edges of the 1024
+every F_i[j] bit for bit the minimum over all predecessors (sampled columns against the
+oracle, every column against the layer-by-layer schedule), at the edges of the 1024
 predecessors of a thread's slot and of the column counts per workgroup, and the
 codebook that the traceback finds."""
 import numpy as np
@@ -52,6 +53,13 @@ def test_held_layers(p, s, kind):
                   pipeline.dp_columns(H, i, lamp, F[i - 1], z, z, cols))[0]
             np.testing.assert_array_equal(F[i, cols], Fo, err_msg=f"{p} {lam} layer {i}")
             assert np.all(np.isinf(F[i, : i - 1])) or i == 2
+        # every column against the layer-by-layer schedule
+        F0, K0, _, _, res0 = ecasq.ecasq_dp_trace(xd, s, lam, schedule=0)
+        F0, K0 = F0.cpu().numpy(), K0.cpu().numpy()
+        for i in range(2, s + 1):
+            np.testing.assert_array_equal(F[i, i - 1:p], F0[i, i - 1:p], err_msg=f"layer {i}")
+            np.testing.assert_array_equal(K[i, i - 1:p], K0[i, i - 1:p], err_msg=f"layer {i}")
+        assert res[:4] == res0[:4]
         # the codebook along the argmins of every layer
         cb, rk, info = ecasq.ecasq_solve_lagrangian(
             xd, s, lam, options=ecasq.ecasq_default_options(refine_rounds=0))
