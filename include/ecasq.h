@@ -15,10 +15,10 @@
  *
  * By default (ecasq_options.dp_schedule = 1) each DP solve keeps F of every
  * layer, O(s d) memory (8 (s+1) d bytes), and the codebook is the argmin
- * traceback of the solve it was found in; `recovery` is then ignored.  The layer-by-layer schedule (dp_schedule = 0)
- * keeps two O(d) layers, as Sec. 5 states the method, and recovers the
- * codebook with Hirschberg's method in O(d) space (recovery = 0) or from
- * stored argmins (recovery = 1).
+ * traceback of the solve it was found in; `recovery` is then ignored.  The
+ * layer-by-layer schedule (dp_schedule = 0) keeps two O(d) layers, as Sec. 5
+ * states the method, and recovers the codebook with Hirschberg's method in O(d)
+ * space (recovery = 0) or from stored argmins (recovery = 1).
  *
  * Conventions for every entry point:
  *   - Array arguments named x, codebook*, symbols, hist, t_out, infos_dev and
@@ -467,13 +467,15 @@ int32_t ecasq_inspect_results(double *lams, int32_t *chains, int32_t cap);
  * search pass, 2 = a whole solve of DP schedule 1 (all its launches, from
  * the first to eq. apx_final, timed as one unit; one that is stopped and
  * solved again by the sweep counts twice; cells are every cell of the program,
- * as for schedule 0, also where only a part of them is evaluated), 3 = one layer of the optimal DP (cells = its (k, l, j)
- * candidates), 4 = one launch of ecasq_solve_batched (cells not counted).
+ * as for schedule 0, also where only a part of them is evaluated), 3 = one
+ * layer of the optimal DP (cells = its (k, l, j) candidates), 4 = one launch of
+ * ecasq_solve_batched (cells not counted).
  * ecasq_timing_read returns, for one variant, the summed milliseconds, the
- * number of timed launches and the (column, predecessor) cells those launches
- * evaluated, each cell for every multiplier of its launch (host pointers, any
- * may be NULL); reset != 0 clears that variant's totals.  on = 2 also prints one line per DP solve to stderr (multiplier,
- * H(I,B), vNMSE, values, elapsed time), for long runs.  Not thread-safe.
+ * number of timed launches and their (column, predecessor) cells, each cell
+ * for every multiplier of its launch (host pointers, any may be NULL);
+ * reset != 0 clears that variant's totals.  on = 2 also prints one line per DP
+ * solve to stderr (multiplier, H(I,B), vNMSE, values, elapsed time), for long
+ * runs.  Not thread-safe.
  */
 void ecasq_timing_enable(int32_t on);
 void ecasq_timing_read(int32_t variant, double *layer_ms, int64_t *layer_launches,
