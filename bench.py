@@ -98,9 +98,9 @@ SWEEP_SOURCES = ("sweep.hip", "device.hpp", "launch.hpp", "log2_table.inc")
 # the same of the layers with bounds (profiles/k_layer_weights_256k.md): bytes per
 # launch, and over all launches of the default workload's solves
 LAYER_TRAFFIC_BYTES_PER_LAUNCH = 3.84e7
-LAYER_COUNTER_FP64_TFLOPS = 10.0
-LAYER_COUNTER_VALU_BUSY = 0.455
-LAYER_SHA = "bfffcf751e7c8ed5"
+LAYER_COUNTER_FP64_TFLOPS = 10.2
+LAYER_COUNTER_VALU_BUSY = 0.458
+LAYER_SHA = "64b7b1bd263dec22"
 LAYER_SOURCES = ("layers.hip", "device.hpp", "launch.hpp", "log2_table.inc")
 # the (workload, s) both traffic figures were measured on; null for others
 TRAFFIC_WORKLOAD = ("weights_256k", 32)

@@ -47,13 +47,13 @@
 // computed frequencies then pass 1, h is negative there, and so are the bounds.
 //
 // What bounds it: the latency of a workgroup's stages, about 30 us a layer at 16384
-// values (1024 workgroups, of which 768 fit the chip at once: three wavefronts a SIMD at 139 to
-// 146 registers), and with many values the work left: 160 us a layer at 2^18 at lambda = 0, 240
-// above, where VALU issue is 45% used and wavefronts wait half of their time for data
-// or at barriers.  2^18 weight-like values, 32 layers: 5.6 ms at lambda = 0, 12.2 at 0.01,
-// 8.6 at 0.1 to 2, where the sweep over all pairs takes 95 and 132 ms; of the p^2 / 2
-// pairs of a layer 0.03% to 0.2% are evaluated and 0.05% to 1% tested one by one.  Bounds
-// that are constant over a unit (no lines) left 1% to 3% and took twice to three
+// values (1024 workgroups, of which 768 fit the chip at once: three wavefronts a SIMD at 137
+// and 168 registers), and with many values the work left: 160 us a layer at 2^18 at
+// lambda = 0, 235 above, where VALU issue is 46% used and wavefronts wait 40% of their time
+// for data or at barriers.  2^18 weight-like values, 32 layers: 5.6 ms at lambda = 0, 12.2
+// at 0.01, 8.6 at 0.1 to 2, where the sweep over all pairs takes 95 and 132 ms; of the
+// p^2 / 2 pairs of a layer 0.03% to 0.2% are evaluated and 0.05% to 1% tested one by one.
+// Bounds that are constant over a unit (no lines) left 1% to 3% and took twice to three
 // times as long.
 #include "device.hpp"
 #include "launch.hpp"
@@ -72,13 +72,13 @@ constexpr int kList = 1024;   // blocks tested per round (those left are listed 
 // of the predecessors where prefix sums cancel so far that no bound holds (values over 60
 // decades, an outlier of 1e18), and then the sweep, which forms each cost once for all
 // layers, is up to ten times faster (2^18 such values, 32 layers: 1390 ms against 132).  So the
-// steps are counted: a workgroup reports its own, at its end and (64 columns) between
-// rounds, once a wavefront has p / 32 of them in a layer (fewer for many layers; most never
-// do), and adds them to a word only where needed, since additions to one word wait for each
-// other, 6 ns each.  When the longest chains of the layers and a kCrowd-th of all steps pass
-// the layer's limit, the solve gives up (the failure word is kSweepGaveUp) and the host
-// takes the sweep: 161 ms in that example, 3.4 against 2.9 for 16384 values.  Counting costs
-// ordinary inputs 0 to 1.5%.
+// steps are counted: a workgroup reports its own at its end if a wavefront has p / 32 of them
+// (fewer for many layers; most never do), and adds them to a word only where needed, since
+// additions to one word wait for each other, 6 ns each.  When the longest chains of the
+// layers and a kCrowd-th of all steps pass the layer's limit, the solve gives up (the
+// failure word is kSweepGaveUp) and the host takes the sweep: 203 ms in that example, 3.4
+// against 2.9 for 16384 values.  Counting costs ordinary inputs 0 to 1.5% (a report between
+// rounds too, which can stop a layer half way, 1 to 2.5%; the example then takes 169 ms).
 struct LayWork {
     unsigned long long all;
     uint32_t chain;       // sum over the layers of the most steps of a wavefront
@@ -480,7 +480,7 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
     __shared__ uint16_t slist[SUP ? kList : 1];
     __shared__ uint16_t list[kList], glist[CW > 1 ? CW : 1][kList], clist[CW][kList];
     __shared__ int32_t nslist, nlist, nglist[CW], nclist[CW];
-    __shared__ uint32_t steps[W], told, stop;
+    __shared__ uint32_t steps[W];
     {
         // three loads in flight together (gone: written by earlier launches only)
         const int32_t run = a.runp ? *a.runp : 1;
@@ -533,7 +533,6 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
         for (int s = 0; s < KS; s++) best = __builtin_fmin(best, red[s][kGC * cg + c]);
     };
     if (tid == 0) {
-        stop = told = 0;
 #pragma unroll
         for (int w = 0; w < W; w++) steps[w] = 0;
         if (blockIdx.x == 0) work_of(a)->longest[(i + 1) & 1] = 0;
@@ -664,14 +663,12 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
             if (most > had) atomicAdd(&work->chain, most - had);
         }
         if (blockIdx.x % kSample == 0) {
-            atomicAdd(&work->all, (unsigned long long)kSample * (sum - told));
-            told = sum;
+            atomicAdd(&work->all, (unsigned long long)kSample * sum);
         }
         if (fresh(&work->chain) + fresh(&work->all) / kCrowd > work->limit[i]) {
             *work->fail = kSweepGaveUp;
             __hip_atomic_store(&work->gone[i & 1], 1u, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
         }
-        stop = fresh(&work->gone[i & 1]);
     };
     auto run = [&](int ns) {
         if (ns == 0) return;
@@ -725,15 +722,9 @@ __global__ __launch_bounds__(64 * CW * KS) void k_layer(LayArgs a, int32_t i) {
         // one round: at most kList units, unit(x) for x < nx
         auto round = [&](int nx, auto unit) {
             __syncthreads();  // the lists are free
-            if (tid == 0) {
-                nlist = 0;
-                if constexpr (SUP) report();  // (else a layer is short)
-            }
+            if (tid == 0) nlist = 0;
             if (tid < CW) nglist[tid] = nclist[tid] = 0;
             __syncthreads();
-            if constexpr (SUP) {
-                if (stop) return;  // uniform
-            }
             uint32_t done = 0;
             for (int x = tid; x < nx; x += T) {
                 const int64_t q = unit(x), dA = q * UN - kA, dB = q * UN - kB;
