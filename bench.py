@@ -143,7 +143,7 @@ def schedule_kernel(p, s):
     """The kernel that schedule 1 takes for p values and s (the library's rule) and its
     launches in one solve."""
     I = min(s, p)
-    if p > 4096 and p > 3072 + 64 * I:
+    if p > 4096 and p > 64 * I and p * p > 800000 * I:
         return "k_layer", I - 1  # and k_layer_base
     if 256 < p <= 4096 and p > 4 * I:
         return "k_held", 2       # and k_held_base

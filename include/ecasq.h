@@ -179,8 +179,8 @@ ecasq_status ecasq_solve(const void *x, ecasq_dtype dt, int64_t d, int32_t s,
  *        - with every cost held in registers, formed once (256 < p <= 4096,
  *          p > 4 I);
  *        - layer by layer with bounds that leave only predecessors that may hold
- *          a minimum to evaluate (p > 4096, p > 3072 + 64 I; a solve whose
- *          prefix sums cancel so far that the bounds hold nothing is
+ *          a minimum to evaluate (p > 4096, p > 64 I, p^2 > 800000 I; a solve
+ *          whose prefix sums cancel so far that the bounds hold nothing is
  *          stopped and solved by the sweep);
  *        - by one sweep over column blocks in which the interval cost and
  *          entropy term of each cell serve every layer (all others).

@@ -1348,14 +1348,19 @@ size_t sweep_scratch_bytes(int64_t d) {
 size_t sweep_cost_bytes() { return (size_t)kQAll * sizeof(double); }
 
 // Above these sizes the layers with bounds (launch_layers) take the sweep's place: a layer's
-// launch takes 20 us at least, so few values for each layer are solved faster by
-// the sweep's chain of blocks.  Sweep / layers in ms on normal values (lambda 0.01, 0.3; at
-// lambda = 0 the layers are faster everywhere): 4097 values, 16 layers 0.54 / 0.32, 0.52 /
-// 0.36, 32 layers 0.80 / 0.70, 0.72 / 0.73; 6000 values, 48 layers 1.34 / 1.21, 1.22 / 1.22, 64
-// layers 1.51 / 1.57, 1.37 / 1.59; 8000 values, 64 layers 1.99 / 1.63, 1.84 / 1.69, 96 layers
-// 2.47 / 2.33, 2.30 / 2.41; 12 000 values, 128 layers 4.44 / 3.71, 4.18 / 3.58; 2^18, 32
-// layers 134 / 8.3.
-bool use_layers(int64_t p, int32_t I) { return p > kHeldMaxP && p > 3072 + 64 * (int64_t)I; }
+// launch takes 20 us at least and every layer scans its columns, so few values for each layer
+// are solved faster by the sweep's chain of blocks, whose work grows with p^2.  The line is
+// p^2 = 800 000 I and p = 64 I, the latter above 195 layers.  Sweep / layers in ms on normal
+// values at lambda 0, 0.001, 0.05, 1: on the line 12 000 values, 180 layers 6.5 / 3.4, 6.3 /
+// 5.7, 5.5 / 4.9, 5.4 / 6.4; above it 15 000 values, 230 layers 9.7 / 6.0, 9.2 / 9.0, 8.4 /
+// 8.3, 8.2 / 7.1 and, at lambda 0, 0.01, 0.3, 4097 values, 20 layers 0.70 / 0.28, 0.72 / 0.42,
+// 0.69 / 0.45; below it, where large multipliers lose more and more, 4097 values, 32 layers
+// 0.77 / 0.44, 0.80 / 0.58, 0.75 / 0.70, 0.71 / 0.87; 6000 values, 51 layers 1.42 / 0.76, 1.45 /
+// 1.07, 1.33 / 1.18, 1.26 / 1.50 (student t 1.29 / 2.01); 9000 values, 115 layers 3.5 / 1.9,
+// 3.5 / 3.0, 3.0 / 2.9, 3.0 / 3.3.  2^18 values, 32 layers at 0.1: 134 / 8.3.
+bool use_layers(int64_t p, int32_t I) {
+    return p > kHeldMaxP && p > 64 * (int64_t)I && p > 800000 * (int64_t)I / p;
+}
 
 // Up to kHeldMaxP values the costs fit in registers (launch_held).  With few values in all, or
 // for each layer, the sweep's chain of blocks is as short as a hand-over between workgroups

@@ -68,8 +68,9 @@ def test_no_rate_where_cells_are_left_out():
 
 @pytest.mark.parametrize("p,s,kernel", [
     (256, 8, "k_sweep_step"), (257, 8, "k_held"), (257, 64, "k_held"), (256, 64, "k_sweep_step"),
-    (4096, 200, "k_held"), (4097, 16, "k_layer"), (4097, 17, "k_sweep_step"),
-    (12000, 139, "k_layer"), (12000, 140, "k_sweep_step")])
+    (4096, 200, "k_held"), (4097, 20, "k_layer"), (4097, 21, "k_sweep_step"),
+    (12000, 179, "k_layer"), (12000, 180, "k_sweep_step"), (12801, 200, "k_layer"),
+    (12800, 200, "k_sweep_step")])
 def test_schedule_kernel(p, s, kernel):
     assert bench.schedule_kernel(p, s)[0] == kernel
 

@@ -1,5 +1,5 @@
-"""The layers with bounds (schedule 1 above 4096 distinct values and 64 per
-layer): every F_i[j] must be the minimum over all predecessors bit for bit, so
+"""The layers with bounds (schedule 1 above 4096 distinct values, few layers to
+them): every F_i[j] must be the minimum over all predecessors bit for bit, so
 no bound may discard one that holds it.  Sampled columns of every layer against
 the oracle's recomputation, which scans every predecessor of the GPU's previous
 layer; sizes at the edges of the 16- and 64-column workgroups and on both sides
@@ -10,6 +10,7 @@ import pytest
 
 torch = pytest.importorskip("torch")
 
+from bench import schedule_kernel
 from oracle import pipeline
 from paper_2608_18147_amd import ecasq, inputs
 
@@ -43,8 +44,8 @@ def _outliers(n, big):
 
 CASES = [
     ("normal_4097", lambda: _distinct(inputs.normal(5000, 1), 4097), 20),
-    ("normal_4112", lambda: _distinct(inputs.normal(5000, 2), 4112), 33),
-    ("lognormal_6145", lambda: _distinct(inputs.lognormal_signed(7000, 3), 6145), 64),
+    ("normal_4112", lambda: _distinct(inputs.normal(5000, 2), 4112), 21),
+    ("lognormal_6145", lambda: _distinct(inputs.lognormal_signed(7000, 3), 6145), 47),
     ("integers_5000", lambda: np.arange(5000, dtype=np.float32), 24),
     ("clusters_6000", lambda: _distinct(_clusters(6400), 6000), 16),
     ("wide_range_6000", lambda: _distinct(_wide(6200), 6000), 12),
@@ -64,7 +65,7 @@ def test_layers_hold_every_minimum(case):
     x = make()
     H = pipeline.prepare(x)
     p = H.p
-    assert p > 4096 and p > 64 * s, "sizes that take the layers with bounds"
+    assert schedule_kernel(p, s)[0] == "k_layer"
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     xd = torch.from_numpy(np.ascontiguousarray(x)).to("cuda")
@@ -107,7 +108,7 @@ def test_layers_where_sums_cancel(n, s, centre, spread, big):
     x = _cancelled(n, centre, spread, big)
     xd = torch.from_numpy(x).to("cuda")
     p = np.unique(x).size
-    assert p > 4096 and p > 64 * s
+    assert schedule_kernel(p, s)[0] == "k_layer"
     opts = [ecasq.ecasq_default_options(dp_schedule=1, refine_rounds=0),
             ecasq.ecasq_default_options(dp_schedule=0, recovery=1, refine_rounds=0)]
     for lam in (0.0, 0.003, 0.2, 50.0):
@@ -149,7 +150,7 @@ def test_layers_on_a_uniform_grid(m, s, kind):
             ecasq.ecasq_solve_lagrangian(xd, s, lam, options=ecasq.ecasq_default_options(
                 alphabet=1, alphabet_size=m, refine_rounds=0, **kw))
             for kw in (dict(dp_schedule=1), dict(dp_schedule=0, recovery=1)))
-        assert i1["p"] > 4096 and i1["p"] > 64 * s, "sizes that take the layers with bounds"
+        assert schedule_kernel(i1["p"], s)[0] == "k_layer"
         assert torch.equal(k1, k0) and torch.equal(c1, c0) and i1["mse"] == i0["mse"]
 
 
@@ -161,7 +162,7 @@ def test_layers_that_give_up(n, s):
     if not torch.cuda.is_available():
         pytest.skip("no GPU")
     x = _wide(n)
-    assert np.unique(x).size > max(4096, 3072 + 64 * s)
+    assert schedule_kernel(np.unique(x).size, s)[0] == "k_layer"
     xd = torch.from_numpy(x).to("cuda")
 
     def opt(**kw):
